@@ -387,7 +387,7 @@ class Plan:
                                               _stream_ptr(stream)))
 
     def set_gridder_occupancy(self, waves_per_simd: int):
-        """Matrix-core gridder build: 6 or 7 waves per SIMD, 0 = by work-item count."""
+        """Accepts 0, 6 or 7; one build of the matrix-core gridder serves all (see ivx_set_gridder_occupancy)."""
         self._check(self.lib.ivx_set_gridder_occupancy(self._h, int(waves_per_simd)))
 
     def set_fused_fold(self, mode: int):

@@ -118,7 +118,6 @@ struct ivx_plan {
     int lanes = 16;
     int vpi = 2;
     int chunk_max = 256;
-    int occupancy = GRIDMX_OCC_AUTO; // matrix-core gridder register budget (waves per SIMD)
     int fused_fold = 1;              // slot fold inside the inverse column pass: 0 never, 1 when it pays, 2 always
     // every call that reuses the evaluation buffers advances the epoch; ivx_objective_backward
     // needs the buffers exactly as ivx_objective_forward left them
@@ -330,6 +329,18 @@ bool tile_fits(const ivx_plan *p, int T, int nwave, int lanes) {
     return grid_lds_bytes(g, nwave, lanes) <= 80 * 1024; // two blocks per 160 KB compute unit
 }
 
+// Kernel shape beta of width W at oversampling sigma: 2.30 W (1 - 1 / (2 sigma)) / 0.75, rounded so
+// that esc = 2 beta log2(e) / W has at most 21 bits.  The matrix-core gridder's exponent
+// esc sqrt(W^2 / 4 - z^2) - esc W / 2 then has exact FP32 constants, and its weights and the
+// deapodization belong to one kernel: a rounded constant would scale all weights alike (2.9e-6 of
+// the gradient at W = 7).
+double es_shape(int W, double sigma, double *esc) {
+    const double beta = 2.30 * W * (1.0 - 1.0 / (2.0 * sigma)) / 0.75;
+    const double e = std::round(std::ldexp(2.0 * beta * M_LOG2E / W, 17)) / std::ldexp(1.0, 17);
+    if (esc) *esc = e;
+    return 0.5 * W * e / M_LOG2E;
+}
+
 // NUFFT geometry: fine grid n_f, kernel width W, kernel shape beta (scaled from the 2.30 W of
 // two-fold oversampling), deapodization 1 / phi_hat at the sub-image frequencies, twiddles.
 void set_geometry_fields(ivx_plan *p, int W, int nf) {
@@ -340,7 +351,7 @@ void set_geometry_fields(ivx_plan *p, int W, int nf) {
     g.W = W;
     g.O = (W + 1) / 2;
     const double sigma = (double)nf / g.nk;
-    p->beta = 2.30 * W * (1.0 - 1.0 / (2.0 * sigma)) / 0.75;
+    p->beta = es_shape(W, sigma, &g.esc);
     g.beta = (real)p->beta;
     g.r_stride = (int64_t)g.nk * g.rw;
     g.hs_stride = (int64_t)g.nf * g.rw;
@@ -366,7 +377,7 @@ void set_geometry_fields(ivx_plan *p, int W, int nf) {
 // its error is at most about twice this.
 double nufft_probe_error(int nk, int nf, int W) {
     const double sigma = (double)nf / nk;
-    const double beta = 2.30 * W * (1.0 - 1.0 / (2.0 * sigma)) / 0.75;
+    const double beta = es_shape(W, sigma, nullptr);
     std::vector<double> gx, gw;
     gauss_legendre(std::max(64, 8 * W), gx, gw);
     double worst = 0.0;
@@ -841,7 +852,7 @@ ivx_status eval_objective(ivx_plan *p, const real *sky, real *grad, double *term
     {
         StageTimer t(p, st, IVX_STAGE_GRID);
         IVX_HIP(launch_grid(MODE_OBJ, g, p->d_work, p->n_work, p->d_crd, p->d_vis, p->d_wgt, p->d_perm, p->d_boff, p->d_ext,
-                            p->d_slots, p->d_jpart, nullptr, nullptr, p->nwave, p->lanes * 10 + p->vpi, p->occupancy, st));
+                            p->d_slots, p->d_jpart, nullptr, nullptr, p->nwave, p->lanes * 10 + p->vpi, st));
     }
     if (use_fused_fold(p)) {
         StageTimer t(p, st, IVX_STAGE_COL_INV); // the fold happens inside this stage
@@ -890,8 +901,7 @@ ivx_status eval_value(ivx_plan *p, const real *sky, double *terms_dev, int grid_
     IVX_HIP(launch_image_rows(g, sky, p->d_beams, p->d_interp, p->d_fscale, p->d_dq, p->d_tw, p->d_R, st));
     IVX_HIP(launch_col_fwd(g, p->d_R, p->d_tw, p->d_ext, st));
     IVX_HIP(launch_grid(grid_mode, g, p->d_work, p->n_work, p->d_crd, p->d_vis, p->d_wgt, p->d_perm, p->d_boff,
-                        p->d_ext, p->d_slots, p->d_jpart, nullptr, nullptr, p->nwave, p->lanes * 10 + p->vpi,
-                        p->occupancy, st));
+                        p->d_ext, p->d_slots, p->d_jpart, nullptr, nullptr, p->nwave, p->lanes * 10 + p->vpi, st));
     const bool sd = sd_active(p);
     if (sd) {
         IVX_HIP(launch_sd_rows(g, sky, p->d_gB, p->sd_rb, p->d.sd_n, p->d.sd_stride, p->d.sd_offset, p->d_U, st));
@@ -1113,7 +1123,7 @@ ivx_status w_forward_planes(ivx_plan *p, const real *sky, hipStream_t st) {
         }
         StageTimer t(p, st, IVX_STAGE_GRID);
         IVX_HIP(launch_wgrid(MODE_WFWD, g, p->d_work, p->n_work, p->d_crd, p->d_ext, p->d_slots, wplane(p, pl, false),
-                             p->nwave, p->lanes * 10 + p->vpi, p->occupancy, st));
+                             p->nwave, p->lanes * 10 + p->vpi, st));
     }
     return IVX_OK;
 }
@@ -1128,7 +1138,7 @@ ivx_status w_adjoint_planes(ivx_plan *p, hipStream_t st) {
         {
             StageTimer t(p, st, IVX_STAGE_GRID);
             IVX_HIP(launch_wgrid(MODE_WADJ, g, p->d_work, p->n_work, p->d_crd, p->d_ext, p->d_slots,
-                                 wplane(p, pl, true), p->nwave, p->lanes * 10 + p->vpi, p->occupancy, st));
+                                 wplane(p, pl, true), p->nwave, p->lanes * 10 + p->vpi, st));
         }
         {
             StageTimer t(p, st, IVX_STAGE_FOLD);
@@ -1362,7 +1372,7 @@ ivx_status ivx_set_gridder_occupancy(ivx_plan *p, int32_t waves_per_simd) {
     if (!p) return fail(IVX_EINVAL, "plan is NULL");
     if (!(waves_per_simd == 0 || waves_per_simd == 6 || waves_per_simd == 7))
         return fail(IVX_EINVAL, "waves_per_simd must be 0 (automatic), 6 or 7");
-    p->occupancy = waves_per_simd;
+    // one build serves every setting (include/ivx.h)
     drop_graph(p); // the captured launches name the build
     return IVX_OK;
 }
@@ -1805,7 +1815,7 @@ ivx_status ivx_forward(ivx_plan *p, const ivx_real *sky, ivx_real *model_vis, vo
     if ((s = run_forward_half(p, sky, st)) != IVX_OK) return s;
     IVX_HIP(launch_zero(model_vis, p->m_total * 2 * (int64_t)sizeof(real), st));
     IVX_HIP(launch_grid(MODE_FWD, p->g, p->d_work, p->n_work, p->d_crd, p->d_vis, p->d_wgt, p->d_perm, p->d_boff, p->d_ext,
-                        p->d_slots, p->d_jpart, nullptr, reinterpret_cast<cpx *>(model_vis), p->nwave, p->lanes * 10 + p->vpi, p->occupancy, st));
+                        p->d_slots, p->d_jpart, nullptr, reinterpret_cast<cpx *>(model_vis), p->nwave, p->lanes * 10 + p->vpi, st));
     return IVX_OK;
 }
 
@@ -1816,7 +1826,7 @@ ivx_status ivx_adjoint(ivx_plan *p, const ivx_real *vis, ivx_real *image, void *
     hipStream_t st = (hipStream_t)stream;
     if (p->w_on) return w_adjoint_call(p, vis, image, false, st);
     IVX_HIP(launch_grid(MODE_ADJ, p->g, p->d_work, p->n_work, p->d_crd, p->d_vis, p->d_wgt, p->d_perm, p->d_boff, p->d_ext,
-                        p->d_slots, p->d_jpart, reinterpret_cast<const cpx *>(vis), nullptr, p->nwave, p->lanes * 10 + p->vpi, p->occupancy, st));
+                        p->d_slots, p->d_jpart, reinterpret_cast<const cpx *>(vis), nullptr, p->nwave, p->lanes * 10 + p->vpi, st));
     if ((s = run_adjoint_half(p, st)) != IVX_OK) return s;
     IVX_HIP(launch_sky(p->g, image, p->d_gp, p->d_cptr, p->d_cent, real(0), real(0), nullptr, nullptr, 0, 0, 1, 0,
                        image, p->d_rpart, SKY_ADJOINT, real(1), st));
@@ -1874,7 +1884,7 @@ ivx_status ivx_forward_adjoint(ivx_plan *p, const ivx_real *vis, ivx_real *image
     if (p->w_on) return w_adjoint_call(p, vis, image, true, st);
     IVX_HIP(launch_grid(MODE_ADJ, p->g, p->d_work, p->n_work, p->d_crd, p->d_vis, p->d_wgt, p->d_perm, p->d_boff,
                         p->d_ext, p->d_slots, p->d_jpart, reinterpret_cast<const cpx *>(vis), nullptr, p->nwave,
-                        p->lanes * 10 + p->vpi, p->occupancy, st, true));
+                        p->lanes * 10 + p->vpi, st, true));
     if ((s = run_adjoint_half(p, st)) != IVX_OK) return s;
     IVX_HIP(launch_sky(p->g, image, p->d_gp, p->d_cptr, p->d_cent, real(0), real(0), nullptr, nullptr, 0, 0, 1, 0,
                        image, p->d_rpart, SKY_ADJOINT, real(1), st));

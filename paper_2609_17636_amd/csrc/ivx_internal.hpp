@@ -55,6 +55,7 @@ struct Geom {
     int rw;               // nf/2 + 1 stored half-plane columns
     int W, O;             // kernel width, extended-grid offset
     real beta;            // ES kernel shape
+    double esc;           // 2 beta log2(e) / W (at most 21 bits)
     int T, win, ldw;      // tile edge, window edge T+W-1, LDS window row stride
     int eh, ew;           // extended grid rows / columns
     int nty, ntx;         // tiles per block along rows / columns
@@ -119,7 +120,7 @@ hipError_t launch_grid(int mode, const Geom &g, const WorkItem *work, int n_work
                        const VisCoord *crd, const cpx *vis, const real *wgt,
                        const int32_t *perm, const int64_t *boff, const cpx *ext, cpx *slots, double *jpart,
                        const cpx *caller_in, cpx *caller_out, int nwave, int variant,
-                       int occupancy, hipStream_t st, bool unweighted = false);
+                       hipStream_t st, bool unweighted = false);
 // adjoint extended grid: the windows summed into `ext` (the forward extended grid, which
 // the gridding pass has consumed by then)
 // sact (may be NULL: every slot counts) flags the slots whose windows were written; the others
@@ -258,22 +259,17 @@ hipError_t launch_win(const WorkItem *work, int n_work, const WGeom &wg, const W
                       const int64_t *boff, const real *wgt, bool unweighted, const cpx *in, cpx *q, hipStream_t st);
 
 // w-stacked gridding pass of one plane, mode MODE_WFWD or MODE_WADJ: on the matrix cores
-// when variant = GRID_MFMA_VARIANT (float build, windows of at most 16 x 16 cells; occupancy
-// as for launch_grid), else the vector gridder (16-lane groups, one visibility per group per
+// when variant = GRID_MFMA_VARIANT (float build, windows of at most 16 x 16 cells), else the vector gridder (16-lane groups, one visibility per group per
 // iteration, nwave waves per work item); prepare_wgrid raises the vector gridder's
 // dynamic-LDS limit (call before any stream capture).
 hipError_t launch_wgrid(int mode, const Geom &g, const WorkItem *work, int n_work, const VisCoord *crd,
-                        const cpx *ext, cpx *slots, const WPlane &wp, int nwave, int variant, int occupancy,
-                        hipStream_t st);
+                        const cpx *ext, cpx *slots, const WPlane &wp, int nwave, int variant, hipStream_t st);
 hipError_t prepare_wgrid(const Geom &g, int nwave);
 
 // Gridding on the matrix cores (float build, windows of at most 16 x 16 cells, one wave
 // per work item): selected by lanes = GRID_MFMA_LANES, variant = GRID_MFMA_VARIANT.
 constexpr int GRID_MFMA_LANES = 64;
 constexpr int GRID_MFMA_VARIANT = 10 * GRID_MFMA_LANES + 1;
-// Register budget of the matrix-core gridder build: waves per SIMD it is compiled for (6 or 7),
-// or 0 to choose by the number of work items.
-constexpr int GRIDMX_OCC_AUTO = 0;
 // Raise the dynamic-LDS limit of the gridding kernels for this geometry (call before any
 // stream capture).
 // variant = 10 * lanes per visibility (8 or 16) + visibilities per group per iteration (1, 2)

@@ -248,6 +248,8 @@ struct GridArgs {
     const int32_t *wcnt; // record counts below each half plane per work item, or NULL
     int wncnt;
     uint8_t *wsact;      // adjoint plane pass: slot written (1) or skipped (0), or NULL
+    float esc, esb;      // matrix-core gridder: phi(z) = 2^(esc sqrt(W^2 / 4 - z^2) - esb)
+    float minus1;        // -1
 };
 
 // Signed distance, in planes, of a record's w from plane p.
@@ -664,17 +666,44 @@ int grid_groups_per_wave(int W, int lanes) { return (lanes == 8 && W <= 8) ? 8 :
 #ifndef IVX_REAL_DOUBLE
 // ---------------------------------------------------- gridding on the matrix cores
 // The same degrid / residual / spread as k_grid, written as per-tile matrix products (float
-// build, windows of at most 16 x 16 cells).  One wave per work item; per batch of 16
-// visibilities the kernel weights of every visibility at the 16 window columns (PX[m][b])
-// and rows (PY[m][a]) -- zero outside its footprint -- go to LDS, then
-//   degrid   Q[a][m] = sum_b F[a][b] PX[m][b]              (v_mfma_f32_16x16x4_f32, K = b)
-//            V_m     = sum_a PY[m][a] Q[a][m]              (4 rows per lane + two lane swaps)
-//   spread   H[a][b] += sum_m PY[m][a] (w_m r_m) PX[m][b]  (v_mfma_f32_16x16x4_f32, K = m)
+// build, windows of at most 16 x 16 cells).  One wave per work item; per batch of 32
+// visibilities, with PX[m][b] and PY[m][a] the kernel weights of visibility m at the window's
+// columns b and rows a (zero outside its footprint),
+//   degrid   Q[a][m] = sum_b F[a][b] PX[m][b]                  (K = b, re and im rows stacked)
+//            V_m     = sum_a PY[m][a] Q[a][m]                  (8 rows per lane, one lane swap)
+//   spread   H[a][b] += sum_m PY[m][a] (w_m r_m) PX[m][b]      (K = m)
 // The window F and the accumulation H stay in registers for the whole work item; H is
-// written to the work item's slot at the end.  Operand layout of the 16x16x4 instruction:
-// lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + v][l % 16].
+// written to the work item's slot at the end.
+//
+// Arithmetic.  Every factor is split into two half-precision parts, x = h + l with h the
+// nearest half and l the nearest half to x - h, and a product is the three matrix products
+// h h' + h l' + l h' accumulated in FP32 (v_mfma_f32_32x32x16_f16, v_mfma_f32_16x16x32_f16).
+// The parts together hold 22 bits and a sign, and the dropped l l' is below 2^-24 of h h', so a
+// product carries the rounding of an FP32 one: against FP64, dot products of 32 and of 256
+// normal deviates are 8.2e-8 and 2.0e-7 off, 1.1e-7 and 2.8e-7 on v_mfma_f32_16x16x4_f32.  Halves
+// reach down to 2^-24, so the window and w r are scaled by powers of two (exactly): the window by
+// its largest value, w r by a scale of the work item that is lowered, with H, when a batch
+// exceeds it; weights are at most 1 and keep 2^-25 of the peak.
+//
+// What bounds it: instruction issue.  A wave64 vector instruction takes 4 cycles of its SIMD, an
+// exponential or square root 8, and a matrix instruction holds the SIMD's issue for 16 whatever
+// its size, so the eight-times cheaper half-precision products leave the vector work (the weights,
+// their splits, the row sum) as the cost.  Each weight is therefore evaluated once, by lane
+// (m = l % 32, axis l / 32), stored to a row of LDS between zeros that are never overwritten, and
+// read back at the window's fixed positions as a row shifted by the footprint's start: no
+// per-batch clearing and no test of the footprint's bounds.  The K = m operands of the spread are
+// rows [m][position] read through the transposing LDS load.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int MX_LD = 17; // row stride of the weight tables (bank spread)
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr int MX_B = 32;             // visibilities per batch
+constexpr int MX_FBITS = 14;         // the window's largest value lies in [2^14, 2^15)
+constexpr int MX_RBITS = 10;         // a new scale puts the largest |w r| in [2^10, 2^11) ...
+constexpr float MX_RMAX = 32768.f;   // ... and is kept while they stay below this (weights are <= 1)
 
 // LDS hand-off between the lanes of the (single-wave) block: a wave's LDS operations are
 // performed in order, so only the compiler has to be kept from moving accesses across;
@@ -685,43 +714,108 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Sum of x over the four 16-lane rows, returned in every lane of the column (lanes l, l ^ 16,
-// l ^ 32, l ^ 48), with the VALU row swaps of gfx950 instead of LDS permutes.  Swapping the
-// odd rows of one copy with the even rows of another and adding gives x[r] + x[r ^ 1] in row
-// r; the same with row pairs {2, 3} <-> {0, 1} completes the sum.  The additions pair the
-// same operands as two xor-shuffle steps (16, then 32), so the result is bitwise the same.
-__device__ __forceinline__ float row_sum4(float x) {
+// Largest x of the wave, in every lane (x >= 0; a NaN is passed over).
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp<0xB1>(x));
+    x = fmaxf(x, dpp<0x4E>(x));
+    x = fmaxf(x, dpp<0x141>(x));
+    x = fmaxf(x, dpp<0x140>(x));
     const unsigned u = __float_as_uint(x);
     const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const float y = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    const unsigned v = __float_as_uint(y);
+    const unsigned v = __float_as_uint(fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1])));
     const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 
-// KW > 0 fixes the kernel width at compile time (the footprint loops unroll without
-// per-lane width tests); KW = 0 reads it from the geometry.  OCC is the occupancy the
-// register allocation aims for: 7 waves per SIMD (72 VGPRs) pays on launches of many work
-// items, 6 (a freer schedule) on launches that fill the chip about once.
-// The w-plane modes of the full model take, as the vector gridder's do, the plane's range of
-// the work item's records (sorted by plane coordinate) and weigh each record by its w kernel
-// at the plane: MODE_WFWD adds w_p V_m to the record's accumulator, MODE_WADJ spreads
-// w_p q_m (q the record's adjoint coefficient).
-template <int MODE, int KW, int OCC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC, 8))) void k_gridmx(GridArgs a) {
-    __shared__ float PX[16 * MX_LD], PY[16 * MX_LD];
-    __shared__ float WRr[16], WRi[16];
+// Sum over the wave, in every lane.
+__device__ __forceinline__ double wave_sum(double x) {
+    x += dpp<0xB1>(x);
+    x += dpp<0x4E>(x);
+    x += dpp<0x141>(x);
+    x += dpp<0x140>(x);
+    const uint2 u = __builtin_bit_cast(uint2, x);
+    const auto p0 = __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false);
+    const auto p1 = __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false);
+    x = __builtin_bit_cast(double, uint2{p0[0], p1[0]}) + __builtin_bit_cast(double, uint2{p0[1], p1[1]});
+    const uint2 v = __builtin_bit_cast(uint2, x);
+    const auto q0 = __builtin_amdgcn_permlane32_swap(v.x, v.x, false, false);
+    const auto q1 = __builtin_amdgcn_permlane32_swap(v.y, v.y, false, false);
+    return __builtin_bit_cast(double, uint2{q0[0], q1[0]}) + __builtin_bit_cast(double, uint2{q0[1], q1[1]});
+}
+
+// Exponent s (|s| <= 126) such that 2^s x lies in [2^(bits), 2^(bits + 1)) as far as s reaches;
+// 0, infinity and NaN give some s in range.
+__device__ __forceinline__ int scale_bits(float x, int bits) {
+    const int e = bits + 127 - (int)((__float_as_uint(x) >> 23) & 0xFF);
+    return e > 126 ? 126 : (e < -126 ? -126 : e);
+}
+
+__device__ __forceinline__ float exp2_int(int e) { return __uint_as_float((unsigned)(e + 127) << 23); } // |e| <= 126
+
+// Eight values as halves hi + lo: x = hi + lo to 2^-25 of the power of two above |x| (and to
+// 2^-25 absolutely).  m1 is -1 in a register the compiler cannot see through: x - hi is then one
+// mixed-precision multiply-add on the half instead of a conversion back and a subtraction.
+__device__ __forceinline__ void split_halves(const float (&x)[8], float m1, f16x8 &hi, f16x8 &lo) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const f32x2 v = {x[2 * i], x[2 * i + 1]};
+        const f16x2 h = __builtin_convertvector(v, f16x2);
+        const f32x2 d = {__builtin_fmaf((float)h[0], m1, v[0]), __builtin_fmaf((float)h[1], m1, v[1])};
+        const f16x2 r = __builtin_convertvector(d, f16x2);
+        hi[2 * i] = h[0];
+        hi[2 * i + 1] = h[1];
+        lo[2 * i] = r[0];
+        lo[2 * i + 1] = r[1];
+    }
+}
+
+// Operand of a K = m product from a table of rows [m][16 positions] of halves: lane (c = l % 16,
+// g = l / 16) receives position c of the rows 4 g .. 4 g + 3 and 16 + 4 g .. 16 + 4 g + 3 (K in an
+// order that both operands share).  A table is stored as two halves of 8 positions, so that the
+// lanes' 16-byte writes are consecutive.  at: this lane's chunk, row 4 g + c / 4, positions
+// 4 (c % 4) .. + 3.
+__device__ __forceinline__ f16x8 column_operand(const _Float16 *at) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    union {
+        s16x4 p[2];
+        f16x8 v;
+    } r;
+    r.p[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
+    r.p[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + 128));
+    return r.v;
+}
+
+// KW > 0 fixes the kernel width at compile time; KW = 0 reads it from the geometry.
+// Measured (gridding of the 36-pointing mosaic, 31.7 M visibilities in 192,831 items / of eight cube
+// channels, 318 M in 1.54 M items / of the 512^2 single pointing): 438 us / 5.01 ms / 19.5 us;
+// the 16-visibility batches of v_mfma_f32_16x16x4_f32 before took 790 us / 7.75 ms / 28.5 us.  A
+// batch takes 155 vector instructions and an item 190: 92% of the issue time on the mosaic.  The LDS
+// (7.7 KB, one table at a time) admits five waves per SIMD; all three tables at once left four
+// (457 us / 5.18 ms), and weight rows by visibility instead of by position cost 512 -> 605 us in
+// bank conflicts.
+template <int MODE, int KW>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_gridmx(GridArgs a) {
+    constexpr bool WPL = MODE == MODE_WFWD || MODE == MODE_WADJ; // one w plane of the full model
+    constexpr bool NOGRID = MODE == MODE_ADJ || MODE == MODE_WADJ; // the grid window is not read
+    constexpr bool SPREAD = MODE == MODE_OBJ || MODE == MODE_ADJ || MODE == MODE_WADJ;
+    constexpr bool DATA = MODE == MODE_OBJ || MODE == MODE_VAL; // residual against the data
+    // Weights, one row of 32 visibilities per position: the x weights in rows XR .. XR + 7, the y
+    // weights in rows YR .. YR + 7, zeros around them.  A footprint starting at window cell i reads
+    // position p at row XR - i + p, i <= 16 - W, p <= 15.  Lane m stays in bank m whatever i is.
+    constexpr int ZR = KW > 0 ? 16 - KW : 12, XR = ZR, YR = XR + 8 + (ZR > 8 ? ZR : 8), NROW = YR + 16;
+    __shared__ __align__(16) float PW[NROW * MX_B];
+    // a table of the spread, hi and lo: PX, then the real and the imaginary part of w r PY in turn
+    constexpr int TH = MX_B * 8 + 32, TB = 2 * TH; // halves of half a table (+ a bank offset), of one table
+    __shared__ __align__(16) _Float16 TS[SPREAD ? 2 * TB : 8];
     const int64_t wid = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     if (wid >= a.n_work) return;
     const WorkItem wi = a.work[wid];
     if (wi.count <= 0) return; // (the work list holds no empty items)
     const Geom &g = a.g;
-    const int l = threadIdx.x, c16 = l & 15, g4 = l >> 4;
+    const int l = threadIdx.x, m = l & 31, hf = l >> 5;
+    const int c16 = l & 15, g4 = l >> 4;
     const int W = KW > 0 ? KW : g.W, win = g.win;
-    constexpr bool WPL = MODE == MODE_WFWD || MODE == MODE_WADJ; // one w plane of the full model
-    constexpr bool NOGRID = MODE == MODE_ADJ || MODE == MODE_WADJ; // the grid window is not read
-    constexpr bool SPREAD = MODE == MODE_OBJ || MODE == MODE_ADJ || MODE == MODE_WADJ;
-    constexpr bool DATA = MODE == MODE_OBJ || MODE == MODE_VAL; // residual against the data
+    const float m1 = a.minus1;
     // the records of this work item that the pass takes: all, or the plane's range
     int base = 0, n = wi.count;
     if constexpr (WPL) {
@@ -748,181 +842,206 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC, 8))) vo
             return;
         }
     }
-    const float zoff = 0.5f * (float)W - 1.f;
-    const float inv_hw = 2.f / (float)W;
-    const float beta2 = g.beta * 1.4426950408889634f;
-    // window F[a][b] (tile rows a, columns b), lane holds F[c16][4 i + g4]
-    float fr[4] = {0.f, 0.f, 0.f, 0.f}, fi[4] = {0.f, 0.f, 0.f, 0.f};
-    if (!NOGRID) {
-        const cpx *F = a.ext + (int64_t)wi.item * g.ext_stride + (int64_t)(wi.tx * g.T) * g.eh + wi.ty * g.T;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int b = 4 * i + g4;
-            if (c16 < win && b < win) {
-                const cpx v = F[b * g.eh + c16];
-                fr[i] = v.re;
-                fi[i] = v.im;
-            }
-        }
-    }
-    f32x4 hre = {0.f, 0.f, 0.f, 0.f}, him = {0.f, 0.f, 0.f, 0.f};
-    float jacc = 0.f;
     const VisCoord *crd = a.crd + wi.begin + base;
-    const cpx *vis = a.vis + wi.begin;
+    const float *vis = reinterpret_cast<const float *>(a.vis + wi.begin);
     const real *wgt = a.wgt + wi.begin;
     const int32_t *perm = a.perm + wi.begin;
     const WZ *wzp = WPL ? a.wz + wi.begin + base : nullptr;
-    cpx *wacc = MODE == MODE_WFWD ? a.wacc + wi.begin + base : nullptr;
-    const cpx *wq = MODE == MODE_WADJ ? a.wq + wi.begin + base : nullptr;
+    float *wacc = MODE == MODE_WFWD ? reinterpret_cast<float *>(a.wacc + wi.begin + base) : nullptr;
+    const float *wq = MODE == MODE_WADJ ? reinterpret_cast<const float *>(a.wq + wi.begin + base) : nullptr;
     const float inv_hww = WPL ? 2.f / (float)a.wW : 0.f;
-    cpx *caller_out = nullptr;
-    const cpx *caller_in = nullptr;
-    if (MODE == MODE_FWD) caller_out = a.caller_out + a.boff[wi.item];
-    if (MODE == MODE_ADJ) caller_in = a.caller_in + a.boff[wi.item];
-    // records of a batch (lanes 0-15); two sets rotate so that the next batch's records are
-    // in flight while the current batch is processed, with no register copies
+    float *caller_out = MODE == MODE_FWD ? reinterpret_cast<float *>(a.caller_out + a.boff[wi.item]) : nullptr;
+    const float *caller_in = MODE == MODE_ADJ ? reinterpret_cast<const float *>(a.caller_in + a.boff[wi.item]) : nullptr;
+    // Records of a batch; two sets rotate so that the next batch's records are in flight while
+    // the current batch is processed.  Lane (m, hf) takes the real (hf = 0) or imaginary
+    // component of visibility m.  Every lane loads, at indices clamped to the last record (a batch
+    // past the end reloads it and ignores it): with no per-lane branches around the loads the
+    // wait before a batch covers only that batch's own loads.
     struct MxRec {
-        VisCoord c; // coordinates of visibility l / 4 of the batch (every lane)
-        cpx y;      // data, weight, caller index of visibility l (lanes 0-15)
-        float w;
+        VisCoord c;
+        float y, w;
         int p;
     };
-    // Every lane loads, at indices clamped to the last record (a batch past the end reloads
-    // it and ignores it): with no per-lane branches around the loads the wait before a batch
-    // covers only that batch's own loads, not the prefetch issued just before it.
+    // (uniform base + 32-bit byte offset, the form the load instructions take)
+    auto at = [](const auto *base, unsigned bytes) {
+        using T = std::remove_cv_t<std::remove_pointer_t<decltype(base)>>;
+        return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + bytes);
+    };
     auto fetch = [&](MxRec &r, int v0) {
-        const int vi = min(v0 + c16, n - 1), vw = min(v0 + (l >> 2), n - 1);
-        r.c = crd[vw];
-        if (DATA) { r.y = vis[vi]; r.w = wgt[vi]; }
-        if (MODE == MODE_ADJ) { r.w = a.unweighted ? 1.f : wgt[vi]; r.p = perm[vi]; }
-        if (MODE == MODE_FWD) r.p = perm[vi];
+        const unsigned o4 = 4u * (unsigned)min(v0 + m, n - 1), o8 = 2 * o4, oc = o8 + 4u * hf;
+        r.c = at(crd, o8);
+        if (DATA) { r.y = at(vis, oc); r.w = at(wgt, o4); }
+        if (MODE == MODE_ADJ) { r.w = a.unweighted ? 1.f : at(wgt, o4); r.p = at(perm, o4); }
+        if (MODE == MODE_FWD) r.p = at(perm, o4);
         if constexpr (WPL) {
             // w carries the record's w-kernel weight at this plane, y its coefficient
-            r.w = es_kernel(wz_dist(wzp[vi], a.wplane), inv_hww, a.wbeta2);
-            if (MODE == MODE_WADJ) r.y = wq[vi];
+            r.w = es_kernel(wz_dist(at(wzp, o4), a.wplane), inv_hww, a.wbeta2);
+            if (MODE == MODE_WADJ) r.y = at(wq, oc);
         }
     };
+    MxRec ra{}, rb{};
+    fetch(ra, 0);
+    // window as the operand [32 rows: re rows 0..15, im rows 0..15][columns 8 hf .. 8 hf + 7].  Cells
+    // past the window repeat its last row or column: their weights are zero.
+    f16x8 fh{}, fl{};
+    float vscale = 0.f;
+    if (!NOGRID) {
+        const float *F = reinterpret_cast<const float *>(a.ext + (int64_t)wi.item * g.ext_stride +
+                                                         (int64_t)(wi.tx * g.T) * g.eh + wi.ty * g.T);
+        float f[8], fm = 0.f;
+        const unsigned row = 8u * min(c16, win - 1) + 4u * (m >> 4), col = 8u * g.eh;
+        if (win == 16) {
+            const unsigned o = row + 8u * hf * col;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = at(F + 2 * j * g.eh, o);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = at(F, row + min(8 * hf + j, win - 1) * col);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fm = fmaxf(fm, fabsf(f[j]));
+        const int sb = scale_bits(wave_max(fm), MX_FBITS);
+        const float sc = exp2_int(sb);
+        vscale = exp2_int(-sb);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f[j] *= sc;
+        split_halves(f, m1, fh, fl);
+    }
+#pragma unroll
+    for (int i = 0; i < NROW * MX_B; i += 256)
+        if (i + 256 <= NROW * MX_B || i + 4 * l < NROW * MX_B) *reinterpret_cast<f32x4 *>(PW + i + 4 * l) = f32x4{0.f, 0.f, 0.f, 0.f};
+    const float hw2 = 0.25f * (float)(W * W), zoff = 0.5f * (float)W - 1.f;
+    const float esc = a.esc, esb = a.esb;
+    f32x4 hre = {0.f, 0.f, 0.f, 0.f}, him = {0.f, 0.f, 0.f, 0.f};
+    float jacc = 0.f;
+    int rbits = 126;              // w r is scaled by 2^rbits
+    float rscale = exp2_int(126);
+    float *prow = PW + (hf ? YR : XR) * MX_B + m;
+    const float *pxr = PW + (XR + 8 * hf) * MX_B + m, *pyr = PW + (YR + 4 * hf) * MX_B + m;
+    const int tw = hf * TH + m * 8, tr = ((c16 >> 1) & 1) * TH + (4 * g4 + (c16 >> 2)) * 8 + 4 * (c16 & 1);
     auto batch = [&](const MxRec &r, int v0) {
-        const bool ok = l < 16 && v0 + c16 < n;
-        if (MODE == MODE_ADJ && l < 16) {
-            float yr = 0.f, yi = 0.f;
-            if (ok) {
-                const cpx y = caller_in[r.p < 0 ? ~r.p : r.p];
-                yr = r.w * y.re;
-                yi = r.w * (r.p < 0 ? -y.im : y.im);
-            }
-            WRr[l] = yr;
-            WRi[l] = yi;
-        }
-        if (MODE == MODE_WADJ && l < 16) {
-            WRr[l] = ok ? r.w * r.y.re : 0.f;
-            WRi[l] = ok ? r.w * r.y.im : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = l + 64 * i, m = e >> 4, pos = e & 15;
-            PX[m * MX_LD + pos] = 0.f;
-            PY[m * MX_LD + pos] = 0.f;
-        }
-        wave_sync();
+        const bool ok = v0 + m < n;
+        // the W weights of axis hf of visibility m (phi at distance z: see es_kernel)
         {
-            // the W nonzero weights per visibility and axis: lane (m = l / 4, k = l % 4 + 4 j),
-            // from the coordinates each lane decoded itself (no hand-off through LDS)
-            const int m = l >> 2;
-            if (v0 + m < n) {
-                int ixm, iym;
-                real fx, fy;
-                decode(r.c, ixm, iym, fx, fy);
-                const float zxm = zoff + fx, zym = zoff + fy;
+            const uint32_t q = hf ? r.c.yq : r.c.xq;
+            const float zf = zoff + (float)(q & 0xFFFFFFu) * 5.9604644775390625e-08f;
 #pragma unroll
-                for (int j = 0; j < (KW > 0 ? (KW + 3) / 4 : 4); ++j) {
-                    const int k = (l & 3) + 4 * j;
-                    if ((KW > 0 && 4 * j + 3 < KW) || k < W) {
-                        PX[m * MX_LD + ixm + k] = es_kernel(zxm - (float)k, inv_hw, beta2);
-                        PY[m * MX_LD + iym + k] = es_kernel(zym - (float)k, inv_hw, beta2);
-                    }
-                }
+            for (int k = 0; k < (KW > 0 ? KW : 8); ++k) {
+                const float z = zf - (float)k; // exact, and |z| <= W / 2
+                const float t = __builtin_fmaf(-z, z, hw2);
+                float w = __builtin_amdgcn_exp2f(__builtin_fmaf(esc, __builtin_amdgcn_sqrtf(t), -esb));
+                if (KW == 0 && k >= W) w = 0.f; // (t may be negative)
+                prow[k * MX_B] = w;
             }
         }
         wave_sync();
-        if (!NOGRID) {
-            f32x4 qre = {0.f, 0.f, 0.f, 0.f}, qim = {0.f, 0.f, 0.f, 0.f};
+        // weights at the window's columns 8 hf + j, and at its rows 4 hf + j (j < 4) and
+        // 4 hf + 4 + j (j >= 4): the rows this lane holds of Q
+        float x[8], y[8];
+        const float *px = pxr - (int)(r.c.xq >> 24) * MX_B, *py = pyr - (int)(r.c.yq >> 24) * MX_B;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float bx = PX[c16 * MX_LD + 4 * i + g4];
-                qre = __builtin_amdgcn_mfma_f32_16x16x4f32(fr[i], bx, qre, 0, 0, 0);
-                qim = __builtin_amdgcn_mfma_f32_16x16x4f32(fi[i], bx, qim, 0, 0, 0);
-            }
+        for (int j = 0; j < 8; ++j) x[j] = px[j * MX_B];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) y[j] = py[(j < 4 ? j : j + 4) * MX_B];
+        wave_sync(); // (the rows are rewritten by the next batch)
+        f16x8 xh, xl, bh, bl;
+        split_halves(x, m1, xh, xl);
+        if (SPREAD) { // PX as the K = m operand
+            *reinterpret_cast<f16x8 *>(TS + tw) = xh;
+            *reinterpret_cast<f16x8 *>(TS + TB + tw) = xl;
+            wave_sync();
+            bh = column_operand(TS + tr);
+            bl = column_operand(TS + TB + tr);
+            wave_sync();
+        }
+        float wr;
+        if (!NOGRID) {
+            f32x16 d = {};
+            d = __builtin_amdgcn_mfma_f32_32x32x16_f16(fl, xh, d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_f16(fh, xl, d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_f16(fh, xh, d, 0, 0, 0);
             float vr = 0.f, vi = 0.f;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float py = PY[c16 * MX_LD + 4 * g4 + v];
-                vr += py * qre[v];
-                vi += py * qim[v];
+            for (int j = 0; j < 8; ++j) {
+                vr += y[j] * d[j];
+                vi += y[j] * d[8 + j];
             }
-            vr = row_sum4(vr);
-            vi = row_sum4(vi);
-            // every lane now holds V of visibility c16 of the batch
+            // both halves' sums: the real part of V_m in lane (m, 0), the imaginary in (m, 1)
+            const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(vr), __float_as_uint(vi), false, false);
+            const float v = (__uint_as_float(p[0]) + __uint_as_float(p[1])) * vscale;
             if (MODE == MODE_FWD) {
-                if (ok) caller_out[r.p < 0 ? ~r.p : r.p] = cpx{vr, r.p < 0 ? -vi : vi};
-                wave_sync();
+                if (ok) caller_out[2 * (int64_t)(r.p < 0 ? ~r.p : r.p) + hf] = r.p < 0 && hf ? -v : v;
                 return;
             }
             if (MODE == MODE_WFWD) {
                 // planes run as successive launches and a record belongs to one work item: a
                 // plain read-modify-write, in plane order
-                if (l < 16 && ok) {
-                    cpx ov = wacc[v0 + c16];
-                    ov.re += r.w * vr;
-                    ov.im += r.w * vi;
-                    wacc[v0 + c16] = ov;
-                }
-                wave_sync();
+                if (ok) wacc[2 * (v0 + m) + hf] += r.w * v;
                 return;
             }
-            if (l < 16) {
-                const float rr = vr - r.y.re, ri = vi - r.y.im;
-                if (ok) jacc += r.w * (rr * rr + ri * ri); // halved at the end
-                if (SPREAD) {
-                    WRr[l] = ok ? r.w * rr : 0.f;
-                    WRi[l] = ok ? r.w * ri : 0.f;
-                }
-            }
-            wave_sync();
+            const float res = v - r.y;
+            wr = ok ? r.w * res : 0.f;
+            if (ok) jacc += r.w * (res * res); // halved at the end
             if (!SPREAD) return;
+        } else if (MODE == MODE_ADJ) {
+            const float yv = caller_in[2 * (int64_t)(r.p < 0 ? ~r.p : r.p) + hf];
+            wr = ok ? r.w * (r.p < 0 && hf ? -yv : yv) : 0.f;
+        } else {
+            wr = ok ? r.w * r.y : 0.f;
         }
+        if (__any(fabsf(wr) * rscale > MX_RMAX)) { // (uniform) lower the scale, and H with it
+            const int nb = scale_bits(wave_max(fabsf(wr)), MX_RBITS), down = nb - rbits;
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            const int m = 4 * s4 + g4;
-            const float ay = PY[m * MX_LD + c16];
-            const float bx = PX[m * MX_LD + c16];
-            hre = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, WRr[m] * bx, hre, 0, 0, 0);
-            him = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, WRi[m] * bx, him, 0, 0, 0);
+            for (int v = 0; v < 4; ++v) {
+                hre[v] = ldexpf(hre[v], down);
+                him[v] = ldexpf(him[v], down);
+            }
+            rbits = nb;
+            rscale = exp2_int(nb);
         }
-        wave_sync(); // the tables are rewritten by the next batch
+        wr *= rscale;
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(wr), __float_as_uint(wr), false, false);
+        const float wre = __uint_as_float(s[0]), wim = __uint_as_float(s[1]);
+#pragma unroll
+        for (int comp = 0; comp < 2; ++comp) {
+            float z[8];
+            f16x8 zh, zl;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) z[j] = (comp ? wim : wre) * y[j];
+            split_halves(z, m1, zh, zl);
+            *reinterpret_cast<f16x8 *>(TS + tw) = zh;
+            *reinterpret_cast<f16x8 *>(TS + TB + tw) = zl;
+            wave_sync();
+            const f16x8 ah = column_operand(TS + tr), al = column_operand(TS + TB + tr);
+            f32x4 &acc = comp ? him : hre;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc, 0, 0, 0);
+            wave_sync(); // the table is rewritten
+        }
     };
-    MxRec ra{}, rb{};
-    fetch(ra, 0);
-    for (int v0 = 0; v0 < n; v0 += 32) {
-        fetch(rb, v0 + 16);
+    wave_sync();
+    for (int v0 = 0; v0 < n; v0 += 2 * MX_B) {
+        fetch(rb, v0 + MX_B);
         batch(ra, v0);
-        if (v0 + 16 >= n) break;
-        fetch(ra, v0 + 32);
-        batch(rb, v0 + 16);
+        if (v0 + MX_B >= n) break;
+        fetch(ra, v0 + 2 * MX_B);
+        batch(rb, v0 + MX_B);
     }
     if (MODE == MODE_FWD || MODE == MODE_WFWD) return;
     if (SPREAD) {
         cpx *Sl = a.slots + (int64_t)wi.slot * g.win_stride; // column-major window
+        // table position 8 h + j holds window row 4 h + j (j < 4) or 4 h + 4 + j
+        const int r0 = 8 * (g4 & 1) + 4 * (g4 >> 1);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int r = 4 * g4 + v;
-            if (r < win && c16 < win) Sl[c16 * win + r] = cpx{hre[v], him[v]};
+            const int r = r0 + v;
+            if (r < win && c16 < win)
+                Sl[c16 * win + r] = cpx{ldexpf(hre[v], -rbits), ldexpf(him[v], -rbits)};
         }
     }
     if (DATA) {
-        double d = 0.5 * (double)jacc;
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) d += __shfl_xor(d, m, 64);
+        const double d = wave_sum(0.5 * (double)jacc);
         if (l == 0) a.jpart[wid] = d;
     }
 }
@@ -1979,25 +2098,18 @@ static hipError_t dispatch(bool prepare, int variant, int mode, const GridArgs &
 }
 
 #ifndef IVX_REAL_DOUBLE
-template <int KW, int OCC> void launch_gridmx_occ(int mode, dim3 grid, const GridArgs &a, hipStream_t st) {
+template <int KW> void launch_gridmx(int mode, dim3 grid, GridArgs a, hipStream_t st) {
+    a.esc = (float)a.g.esc;
+    a.esb = a.esc * (0.5f * (float)a.g.W);
+    a.minus1 = -1.f;
     switch (mode) {
-    case MODE_OBJ: k_gridmx<MODE_OBJ, KW, OCC><<<grid, 64, 0, st>>>(a); break;
-    case MODE_FWD: k_gridmx<MODE_FWD, KW, OCC><<<grid, 64, 0, st>>>(a); break;
-    case MODE_VAL: k_gridmx<MODE_VAL, KW, OCC><<<grid, 64, 0, st>>>(a); break;
-    case MODE_WFWD: k_gridmx<MODE_WFWD, KW, OCC><<<grid, 64, 0, st>>>(a); break;
-    case MODE_WADJ: k_gridmx<MODE_WADJ, KW, OCC><<<grid, 64, 0, st>>>(a); break;
-    default: k_gridmx<MODE_ADJ, KW, OCC><<<grid, 64, 0, st>>>(a); break;
+    case MODE_OBJ: k_gridmx<MODE_OBJ, KW><<<grid, 64, 0, st>>>(a); break;
+    case MODE_FWD: k_gridmx<MODE_FWD, KW><<<grid, 64, 0, st>>>(a); break;
+    case MODE_VAL: k_gridmx<MODE_VAL, KW><<<grid, 64, 0, st>>>(a); break;
+    case MODE_WFWD: k_gridmx<MODE_WFWD, KW><<<grid, 64, 0, st>>>(a); break;
+    case MODE_WADJ: k_gridmx<MODE_WADJ, KW><<<grid, 64, 0, st>>>(a); break;
+    default: k_gridmx<MODE_ADJ, KW><<<grid, 64, 0, st>>>(a); break;
     }
-}
-
-// Work items beyond which the 7-waves-per-SIMD build is used (about four rounds of waves
-// on 1,024 SIMDs).
-constexpr int64_t GRIDMX_OCC7_ITEMS = 32768;
-
-template <int KW> void launch_gridmx(int mode, dim3 grid, const GridArgs &a, int occ, hipStream_t st) {
-    if (occ == GRIDMX_OCC_AUTO) occ = a.n_work >= GRIDMX_OCC7_ITEMS ? 7 : 6;
-    if (occ == 7) launch_gridmx_occ<KW, 7>(mode, grid, a, st);
-    else launch_gridmx_occ<KW, 6>(mode, grid, a, st);
 }
 #endif
 
@@ -2046,12 +2158,10 @@ hipError_t prepare_wgrid(const Geom &g, int nwave) {
 }
 
 hipError_t launch_wgrid(int mode, const Geom &g, const WorkItem *work, int n_work, const VisCoord *crd,
-                        const cpx *ext, cpx *slots, const WPlane &wp, int nwave, int variant, int occupancy,
-                        hipStream_t st) {
+                        const cpx *ext, cpx *slots, const WPlane &wp, int nwave, int variant, hipStream_t st) {
     if (mode != MODE_WFWD && mode != MODE_WADJ) return hipErrorInvalidValue;
     if (n_work <= 0) return hipSuccess;
     if (nwave < 1 || nwave > NT / 64 || wp.W < 2 || wp.W > 16) return hipErrorInvalidValue;
-    if (!(occupancy == GRIDMX_OCC_AUTO || occupancy == 6 || occupancy == 7)) return hipErrorInvalidValue;
     GridArgs a{};
     a.g = g;
     a.work = work;
@@ -2081,9 +2191,9 @@ hipError_t launch_wgrid(int mode, const Geom &g, const WorkItem *work, int n_wor
         const unsigned gx = (unsigned)n_work < GRID_ROW ? (unsigned)n_work : GRID_ROW;
         const dim3 grid(gx, (unsigned)((n_work + gx - 1) / gx));
         switch (g.W) {
-        case 7: launch_gridmx<7>(mode, grid, a, occupancy, st); break;
-        case 8: launch_gridmx<8>(mode, grid, a, occupancy, st); break;
-        default: launch_gridmx<0>(mode, grid, a, occupancy, st); break;
+        case 7: launch_gridmx<7>(mode, grid, a, st); break;
+        case 8: launch_gridmx<8>(mode, grid, a, st); break;
+        default: launch_gridmx<0>(mode, grid, a, st); break;
         }
         return hipGetLastError();
 #endif
@@ -2103,8 +2213,7 @@ hipError_t prepare_grid(const Geom &g, int nwave, int variant) {
 hipError_t launch_grid(int mode, const Geom &g, const WorkItem *work, int n_work, const VisCoord *crd,
                        const cpx *vis, const real *wgt, const int32_t *perm, const int64_t *boff, const cpx *ext,
                        cpx *slots, double *jpart, const cpx *caller_in, cpx *caller_out, int nwave, int variant,
-                       int occupancy, hipStream_t st, bool unweighted) {
-    if (!(occupancy == GRIDMX_OCC_AUTO || occupancy == 6 || occupancy == 7)) return hipErrorInvalidValue;
+                       hipStream_t st, bool unweighted) {
     if (n_work <= 0) return hipSuccess;
     if (nwave < 1 || nwave > NT / 64) return hipErrorInvalidValue;
     GridArgs a{g, work, crd, vis, wgt, perm, boff, ext, slots, jpart, caller_in, caller_out, nwave, n_work,
@@ -2117,9 +2226,9 @@ hipError_t launch_grid(int mode, const Geom &g, const WorkItem *work, int n_work
         const unsigned gx = (unsigned)n_work < GRID_ROW ? (unsigned)n_work : GRID_ROW;
         const dim3 grid(gx, (unsigned)((n_work + gx - 1) / gx));
         switch (g.W) {
-        case 7: launch_gridmx<7>(mode, grid, a, occupancy, st); break;
-        case 8: launch_gridmx<8>(mode, grid, a, occupancy, st); break;
-        default: launch_gridmx<0>(mode, grid, a, occupancy, st); break;
+        case 7: launch_gridmx<7>(mode, grid, a, st); break;
+        case 8: launch_gridmx<8>(mode, grid, a, st); break;
+        default: launch_gridmx<0>(mode, grid, a, st); break;
         }
         return hipGetLastError();
 #endif
