@@ -59,7 +59,7 @@ template <int NTW>
 __global__ __launch_bounds__(NT) void k_conv3x3(const float *__restrict__ x, int n, int h, int w, int cin,
                                                 const uint16_t *__restrict__ wt, const float *__restrict__ bias,
                                                 int cout, int relu, const float *__restrict__ mask, int accumulate,
-                                                float *__restrict__ y) {
+                                                float *__restrict__ y, uint16_t *__restrict__ yb) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t P = (int64_t)n * h * w;
     const int64_t pbase = (int64_t)blockIdx.x * 64 + wave * 16;
@@ -123,244 +123,352 @@ __global__ __launch_bounds__(NT) void k_conv3x3(const float *__restrict__ x, int
             if (relu) val = fmaxf(val, 0.f);
             if (mask && !(mask[o] > 0.f)) val = 0.f;
             if (accumulate) val += y[o];
-            y[o] = val;
+            if (y) y[o] = val;
+            if (yb) yb[o] = f2bf(val);
         }
     }
 }
 
-// LDS-tiled implicit GEMM for the 3x3 convolution: block tile 64 pixels x BN channels
-// (BN = 32 NJ), k chunks of 32 staged in LDS as bf16 (A: [pixel][k], B: [channel][k], rows
-// padded to 40 elements), 4 waves in a 2 x 2 arrangement, each wave 2 x NJ tiles of
-// v_mfma_f32_16x16x32_bf16 (one per chunk).  The next chunk's global loads are issued before
-// the current chunk's matrix products.
-constexpr int TBM = 64, TBK = 32, TLD = 40;
-template <int NJ>
-__global__ __launch_bounds__(NT) void k_conv3x3_tiled(const float *__restrict__ x, int n, int h, int w, int cin,
-                                                      const uint16_t *__restrict__ wt, const float *__restrict__ bias,
-                                                      int cout, int relu, const float *__restrict__ mask,
-                                                      int accumulate, float *__restrict__ y) {
-    constexpr int BN = 32 * NJ;
-    __shared__ __align__(16) uint16_t As[TBM * TLD];
-    __shared__ __align__(16) uint16_t Bs[BN * TLD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// ------------------------------------------------- 3x3 convolution, one wave per output tile
+// Input of a convolution as 8-channel pieces: bf16 activations (16 bytes a piece) or FP32 ones
+// rounded to bf16 as they are loaded.  A second source continues the channels of the first, and the
+// first may be at half resolution: the decoder's concatenation of an upsampled level and a skip is
+// read in place instead of being written out.
+template <typename T> struct ConvIn {
+    const T *x0, *x1; // channels [0, ca) and [ca, cin)
+    int ca;
+    int half0;        // x0 is [n][h / 2][w / 2][ca]
+};
+
+// Output of a convolution: FP32 and / or bf16, [P][cout]; with `split` > 0 the FP32 output is two
+// tensors, channels [0, split) in y and the rest in y1.
+struct ConvOut {
+    float *y, *y1;
+    uint16_t *yb;
+    int split;
+    const float *bias;
+    int relu, accumulate;
+    const float *maskf;      // FP32 mask [P][cout] or NULL
+    ConvIn<uint16_t> maskb;  // bf16 mask (x0 NULL: none)
+};
+
+// Buffer view of `bytes` from p: a load whose offset is not below the view's size returns 0, which is
+// the padding of the image (a lane outside takes NO_PIECE), with no branch and no second address.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr unsigned NO_PIECE = 0x80000000u;
+template <typename T> __device__ __forceinline__ __amdgpu_buffer_rsrc_t view(const T *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(p), 0, (int)(bytes < 0x7FFFFFFF ? bytes : 0x7FFFFFFF), 0x00020000);
+}
+// Eight channels at byte offset vo, as raw bf16 bits.  (No scalar offset: it is taken off the view's
+// size in the range check, which wraps where the size is smaller.)
+template <typename T> __device__ __forceinline__ uint4 load_raw(__amdgpu_buffer_rsrc_t r, unsigned vo) {
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, vo, 0, 0);
+    if constexpr (sizeof(T) == 2) return uint4{a[0], a[1], a[2], a[3]};
+    else {
+        typedef float f32x4_ __attribute__((ext_vector_type(4)));
+        const f32x4_ f = __builtin_bit_cast(f32x4_, a);
+        const f32x4_ g = __builtin_bit_cast(f32x4_, __builtin_amdgcn_raw_buffer_load_b128(r, vo + 16, 0, 0));
+        return __builtin_bit_cast(uint4, bf16x8{(__bf16)f[0], (__bf16)f[1], (__bf16)f[2], (__bf16)f[3], (__bf16)g[0],
+                                                (__bf16)g[1], (__bf16)g[2], (__bf16)g[3]});
+    }
+}
+template <typename T> __device__ __forceinline__ const T *uniform_ptr(const T *p) {
+    const uint64_t u = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = __builtin_amdgcn_readfirstlane((int)(u >> 32));
+    return (const T *)((uint64_t)hi << 32 | lo);
+}
+
+// Four consecutive channels co .. co + 3 of pixel p = (img, py, px): bias, ReLU, mask, sum, store.
+__device__ __forceinline__ void store_out(const ConvOut &out, f32x4 acc, int64_t p, int64_t img, int py, int px, int h,
+                                          int w, int cout, int co) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = acc[e] + (out.bias ? out.bias[co + e] : 0.f);
+        if (out.relu) v[e] = fmaxf(v[e], 0.f);
+    }
+    if (out.maskf) {
+        const float4 q = *reinterpret_cast<const float4 *>(out.maskf + p * cout + co);
+        v[0] = q.x > 0.f ? v[0] : 0.f;
+        v[1] = q.y > 0.f ? v[1] : 0.f;
+        v[2] = q.z > 0.f ? v[2] : 0.f;
+        v[3] = q.w > 0.f ? v[3] : 0.f;
+    }
+    if (out.maskb.x0) { // activations after a ReLU: a positive bf16 is a positive 16-bit integer
+        const bool first = co < out.maskb.ca;
+        const int sh = first ? out.maskb.half0 : 0;
+        const int64_t pix = (img * (h >> sh) + (py >> sh)) * (w >> sh) + (px >> sh);
+        const uint16_t *at = first ? out.maskb.x0 + pix * out.maskb.ca + co
+                                   : out.maskb.x1 + pix * (cout - out.maskb.ca) + (co - out.maskb.ca);
+        const uint2 q = *reinterpret_cast<const uint2 *>(at);
+        v[0] = (int16_t)(q.x & 0xFFFF) > 0 ? v[0] : 0.f;
+        v[1] = (int16_t)(q.x >> 16) > 0 ? v[1] : 0.f;
+        v[2] = (int16_t)(q.y & 0xFFFF) > 0 ? v[2] : 0.f;
+        v[3] = (int16_t)(q.y >> 16) > 0 ? v[3] : 0.f;
+    }
+    if (out.y) {
+        float4 *o = reinterpret_cast<float4 *>(out.split == 0     ? out.y + p * cout + co
+                                               : co < out.split ? out.y + p * out.split + co
+                                                                : out.y1 + p * (cout - out.split) + (co - out.split));
+        if (out.accumulate) {
+            const float4 q = *o;
+            v[0] += q.x;
+            v[1] += q.y;
+            v[2] += q.z;
+            v[3] += q.w;
+        }
+        *o = float4{v[0], v[1], v[2], v[3]};
+    }
+    if (out.yb) {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<uint2 *>(out.yb + p * cout + co) =
+            __builtin_bit_cast(uint2, bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]});
+    }
+}
+
+// Channel counts that the patch kernel below does not take (not both multiples of 32, or more inputs
+// than its patch holds).  Output tile of one wave: 16 MI pixels x 16 NJ channels, K in 32-wide steps, operands
+// straight from global memory (each lane's 8 consecutive k are 16 contiguous bytes of a pixel or of a weight
+// row), DEPTH steps in flight; bound by those loads.
+// The order of the steps fixes the bits of the sums: tap-major, or (chunks) channel-chunk-major.
+// ANYC: cin is a multiple of 8 but not of 32 (a step spans taps).
+template <typename T, int MI, int NJ, int DEPTH, bool ANYC>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 8))) void
+k_conv3x3_wave(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__restrict__ wt, int packed, int cout, int chunks,
+               ConvOut out) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, kq = lane >> 4;
     const int64_t P = (int64_t)n * h * w;
-    const int K = 9 * cin;
-    const int64_t m0 = (int64_t)blockIdx.x * TBM;
-    const int n0 = blockIdx.y * BN;
-    // ---- global -> register staging: A (pixel am, k quarter aq), B (channel rows)
-    const int am = tid >> 2, aq = (tid & 3) * 8;
-    const int64_t ap = m0 + am;
-    int apn = 0, apy = 0, apx = 0;
-    const bool apv = ap < P;
-    if (apv) {
-        apn = (int)(ap / ((int64_t)h * w));
-        const int r = (int)(ap - (int64_t)apn * h * w);
-        apy = r / w;
-        apx = r - apy * w;
+    const int64_t m0 = ((int64_t)blockIdx.x * 4 + wave) * (16 * MI);
+    const int n0 = blockIdx.y * (16 * NJ);
+    if (m0 >= P) return;
+    const int K = 9 * cin, ca = in.ca, cb = cin - in.ca;
+    constexpr int SZ = (int)sizeof(T);
+    const int half0 = in.half0, w2 = w >> 1, h2 = h >> 1;
+    // The wave's pixels start at (img0, py0): its views of the sources start above them, so offsets are
+    // small and not negative whatever the size of the tensor.
+    const int64_t img0 = m0 / ((int64_t)h * w);
+    const int py0 = (int)(m0 - img0 * h * w) / w;
+    const int64_t first1 = m0 - w - 1;                                             // tap (0, 0) of pixel m0
+    const int row0 = py0 > 0 ? (py0 - 1) >> 1 : 0;                                 // its row at half resolution
+    const int64_t first0 = half0 ? (img0 * h2 + row0) * w2 : first1;
+    const __amdgpu_buffer_rsrc_t r0 =
+        view(uniform_ptr(in.x0 + first0 * ca), ((half0 ? (int64_t)n * h2 * w2 : P) - first0) * ca * SZ);
+    const __amdgpu_buffer_rsrc_t r1 = view(uniform_ptr(in.x1 + first1 * cb), (P - first1) * cb * SZ);
+    const __amdgpu_buffer_rsrc_t rw = view(wt + (int64_t)n0 * K, (int64_t)(cout - n0) * K * 2);
+    // pixel of operand row `row` of each tile and the taps that stay inside the image
+    int py[MI], px[MI], ok[MI];
+    int64_t img[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int64_t p = m0 + 16 * i + row, q = p < P ? p : P - 1;
+        img[i] = q / ((int64_t)h * w);
+        const int r = (int)(q - img[i] * h * w);
+        py[i] = r / w;
+        px[i] = r - py[i] * w;
+        const int rows = (py[i] > 0 ? 7 : 0) | 7 << 3 | (py[i] + 1 < h ? 7 << 6 : 0);
+        const int cols = (px[i] > 0 ? 0x49 : 0) | 0x92 | (px[i] + 1 < w ? 0x124 : 0);
+        ok[i] = p < P ? rows & cols : 0;
     }
-    constexpr int BPIECES = BN * (TBK / 8);           // 8-element pieces of one B chunk
-    constexpr int BROWS = (BPIECES + NT - 1) / NT;    // per thread (1 or 2)
-    uint16_t ra[8];
-    uint16_t rb[BROWS][8];
-    auto gload = [&](int k0) {
-#pragma unroll
-        for (int hlf = 0; hlf < 2; ++hlf) {
-            const int k = k0 + aq + 4 * hlf;
-            float4 v = float4{0.f, 0.f, 0.f, 0.f};
-            if (apv && k < K) {
-                const int tap = k / cin, c = k - tap * cin;
-                const int yy = apy + tap / 3 - 1, xx = apx + tap % 3 - 1;
-                if (yy >= 0 && yy < h && xx >= 0 && xx < w)
-                    v = *reinterpret_cast<const float4 *>(x + (((int64_t)apn * h + yy) * w + xx) * cin + c);
-            }
-            ra[4 * hlf + 0] = f2bf(v.x);
-            ra[4 * hlf + 1] = f2bf(v.y);
-            ra[4 * hlf + 2] = f2bf(v.z);
-            ra[4 * hlf + 3] = f2bf(v.w);
-        }
-#pragma unroll
-        for (int b = 0; b < BROWS; ++b) {
-            const int e = tid + b * NT;
-            const int o = e >> 2, bq = (e & 3) * 8;
-#pragma unroll
-            for (int hlf = 0; hlf < 2; ++hlf) {
-                const int k = k0 + bq + 4 * hlf;
-                uint2 u = uint2{0u, 0u};
-                if (e < BPIECES && n0 + o < cout && k < K) u = *reinterpret_cast<const uint2 *>(wt + (int64_t)(n0 + o) * K + k);
-                rb[b][4 * hlf + 0] = (uint16_t)(u.x & 0xFFFFu);
-                rb[b][4 * hlf + 1] = (uint16_t)(u.x >> 16);
-                rb[b][4 * hlf + 2] = (uint16_t)(u.y & 0xFFFFu);
-                rb[b][4 * hlf + 3] = (uint16_t)(u.y >> 16);
-            }
-        }
+    // byte offset of pixel i's channel 0 at a tap, in the half-resolution source
+    auto half_at = [&](int i, int dy, int dx) {
+        return (unsigned)(((int)(img[i] - img0) * h2 - row0 + ((py[i] + dy) >> 1)) * w2 + ((px[i] + dx) >> 1)) *
+               (unsigned)(ca * SZ);
     };
-    auto sstore = [&]() {
-        uint4 va;
-        va.x = ra[0] | ((uint32_t)ra[1] << 16);
-        va.y = ra[2] | ((uint32_t)ra[3] << 16);
-        va.z = ra[4] | ((uint32_t)ra[5] << 16);
-        va.w = ra[6] | ((uint32_t)ra[7] << 16);
-        *reinterpret_cast<uint4 *>(&As[am * TLD + aq]) = va;
+    const int wsh = !ANYC && packed ? 4 : 0; // (packed: a step is 1 KB per 16 channels)
+    const unsigned wlane = wsh ? 16u * lane : (unsigned)(row * K + 8 * kq) * 2u; // (cout is a multiple of 16 NJ)
+    const int nc = cin / 32, steps = ANYC ? (K + 31) / 32 : 9 * nc;
+    int tap = 0, ch = 0, ks = 0; // the next step to load
+    f32x4 acc[NJ][MI];
 #pragma unroll
-        for (int b = 0; b < BROWS; ++b) {
-            const int e = tid + b * NT;
-            if (e >= BPIECES) continue;
-            const int o = e >> 2, bq = (e & 3) * 8;
-            uint4 vb;
-            vb.x = rb[b][0] | ((uint32_t)rb[b][1] << 16);
-            vb.y = rb[b][2] | ((uint32_t)rb[b][3] << 16);
-            vb.z = rb[b][4] | ((uint32_t)rb[b][5] << 16);
-            vb.w = rb[b][6] | ((uint32_t)rb[b][7] << 16);
-            *reinterpret_cast<uint4 *>(&Bs[o * TLD + bq]) = vb;
-        }
-    };
-    // ---- matrix products: wave (wr, wc) owns rows 32 wr .. +32, columns 16 NJ wc .. +16 NJ
-    const int wr = wave >> 1, wc = wave & 1;
-    const int row = lane & 15, kq = lane >> 4;
-    f32x4 acc[2][NJ];
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MI; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint4 av[DEPTH][MI], wv[DEPTH][NJ];
+    // One step of operands (steps past the last load zeros: the products after it add nothing)
+#define IVX_CONV_LOAD(d)                                                                                        \
+    do {                                                                                                        \
+        if (ANYC) { /* a lane's eight k lie in one tap, the lanes' in several */                                \
+            const int k = ks + 8 * kq, t = k / cin, c = k - t * cin, dy = t / 3 - 1, dx = t - 3 * (t / 3) - 1;  \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i) {                                                    \
+                const bool in_k = k < K && ((ok[i] >> t) & 1);                                                  \
+                unsigned o0 = half0 ? half_at(i, dy, dx) : (unsigned)(16 * i + row + (dy + 1) * w + dx + 1) * (unsigned)(ca * SZ); \
+                unsigned o1 = (unsigned)(16 * i + row + (dy + 1) * w + dx + 1) * (unsigned)(cb * SZ);           \
+                const uint4 a0 = load_raw<T>(r0, in_k && c < ca ? o0 + (unsigned)(c * SZ) : NO_PIECE);       \
+                av[d][i] = a0;                                                                                  \
+                if (cb) {                                                                                       \
+                    const uint4 a1 = load_raw<T>(r1, in_k && c >= ca ? o1 + (unsigned)((c - ca) * SZ) : NO_PIECE); \
+                    av[d][i] = uint4{a0.x | a1.x, a0.y | a1.y, a0.z | a1.z, a0.w | a1.w};                       \
+                }                                                                                               \
+            }                                                                                                   \
+            _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                                      \
+                wv[d][j] = load_raw<uint16_t>(rw, k < K ? wlane + (unsigned)(32 * j * K + 2 * ks) : NO_PIECE); \
+            ks += 32;                                                                                           \
+        } else {                                                                                                \
+            const int c = 32 * ch, dy = tap / 3 - 1, dx = tap - 3 * (tap / 3) - 1;                              \
+            const int live = tap < 9 && ch < nc ? 1 : 0;                                                        \
+            if (half0 && c < ca) {                                                                              \
+                _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                  \
+                    av[d][i] = load_raw<T>(r0, (ok[i] >> tap) & live ? half_at(i, dy, dx) + (unsigned)((c + 8 * kq) * SZ) : NO_PIECE); \
+            } else {                                                                                            \
+                const bool a0 = c < ca || cb == 0;                                                              \
+                const int cs = a0 ? ca : cb;                                                                    \
+                const unsigned so = (unsigned)((((dy + 1) * w + dx + 1) * cs + (a0 ? c : c - ca)) * SZ);        \
+                _Pragma("unroll") for (int i = 0; i < MI; ++i) {                                                \
+                    const unsigned vo = (ok[i] >> tap) & live ? (unsigned)(((16 * i + row) * cs + 8 * kq) * SZ) + so : NO_PIECE; \
+                    av[d][i] = a0 ? load_raw<T>(r0, vo) : load_raw<T>(r1, vo);                            \
+                }                                                                                               \
+            }                                                                                                   \
+            _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                                      \
+                wv[d][j] = load_raw<uint16_t>(rw, live ? wlane + (unsigned)(32 * j * K + (2 * (tap * cin + c) << wsh)) : NO_PIECE);                                 \
+            if (chunks) {                                                                                       \
+                if (++tap == 9) tap = 0, ++ch;                                                                  \
+            } else {                                                                                            \
+                if (++ch == nc) ch = 0, ++tap;                                                                  \
+            }                                                                                                   \
+        }                                                                                                       \
+    } while (0)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nch = (K + TBK - 1) / TBK;
-    gload(0);
-    for (int kc = 0; kc < nch; ++kc) {
-        __syncthreads();
-        sstore();
-        __syncthreads();
-        if (kc + 1 < nch) gload((kc + 1) * TBK);
-        static_assert(TBK == 32, "one 16x16x32 product per chunk");
-        bf16x8 af[2], bfr[NJ];
+    for (int d = 0; d < DEPTH; ++d) IVX_CONV_LOAD(d);
+    for (int s0 = 0; s0 < steps; s0 += DEPTH) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            af[i] = as_bf16x8(*reinterpret_cast<const uint4 *>(&As[(wr * 32 + i * 16 + row) * TLD + 8 * kq]));
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            bfr[j] = as_bf16x8(*reinterpret_cast<const uint4 *>(&Bs[(wc * 16 * NJ + j * 16 + row) * TLD + 8 * kq]));
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[i][j] = mma(af[i], bfr[j], acc[i][j]);
-    }
-    // ---- epilogue: D row (pixel) 4 kq + v, column (channel) = row index of the lane
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int co = n0 + wc * 16 * NJ + j * 16 + row;
-            if (co >= cout) continue;
-            const float bb = bias ? bias[co] : 0.f;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t pp = m0 + wr * 32 + i * 16 + 4 * kq + v;
-                if (pp >= P) continue;
-                const int64_t o = pp * cout + co;
-                float val = acc[i][j][v] + bb;
-                if (relu) val = fmaxf(val, 0.f);
-                if (mask && !(mask[o] > 0.f)) val = 0.f;
-                if (accumulate) val += y[o];
-                y[o] = val;
-            }
-        }
-}
-
-// 3x3 convolution for cin % 32 == 0 on a 2-D output patch: a block computes 4 x 16 output
-// pixels (one image) x BN = 32 NJ channels.  Per chunk of 32 input channels it stages the
-// patch with its one-pixel halo (6 x 18 pixels, bf16) and the chunk's weights of all nine taps
-// in LDS once, and takes the A operand of every tap from the staged patch: each input value
-// is read from memory once per block instead of once per tap.  4 waves in a 2 x 2
-// arrangement as in k_conv3x3_tiled; one v_mfma_f32_16x16x32_bf16 per tap and chunk.
-constexpr int HX_TH = 4, HX_TW = 16, HX_PH = HX_TH + 2, HX_PW = HX_TW + 2, HX_LD = 40;
-template <int NJ>
-__global__ __launch_bounds__(NT) void k_conv3x3_halo(const float *__restrict__ x, int n, int h, int w, int cin,
-                                                     const uint16_t *__restrict__ wt, const float *__restrict__ bias,
-                                                     int cout, int relu, const float *__restrict__ mask,
-                                                     int accumulate, float *__restrict__ y) {
-    constexpr int BN = 32 * NJ;
-    __shared__ __align__(16) uint16_t Ps[HX_PH * HX_PW * HX_LD];
-    __shared__ __align__(16) uint16_t Bs[9 * BN * HX_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tiles_x = (w + HX_TW - 1) / HX_TW, tiles_y = (h + HX_TH - 1) / HX_TH;
-    const int64_t t = blockIdx.x;
-    const int img = (int)(t / ((int64_t)tiles_x * tiles_y));
-    const int rem = (int)(t - (int64_t)img * tiles_x * tiles_y);
-    const int y0 = (rem / tiles_x) * HX_TH, x0 = (rem % tiles_x) * HX_TW;
-    const int n0 = blockIdx.y * BN;
-    const int K = 9 * cin;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int row = lane & 15, kq = lane >> 4;
-    f32x4 acc[2][NJ];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < cin; c0 += 32) {
-        __syncthreads(); // the previous chunk's products are done with the LDS
-        // patch: (6 x 18 positions) x (8 groups of 4 channels), zero outside the image
-        for (int e = tid; e < HX_PH * HX_PW * 8; e += NT) {
-            const int pos = e >> 3, q = e & 7;
-            const int py = y0 - 1 + pos / HX_PW, px = x0 - 1 + pos % HX_PW;
-            float4 v = float4{0.f, 0.f, 0.f, 0.f};
-            if (py >= 0 && py < h && px >= 0 && px < w)
-                v = *reinterpret_cast<const float4 *>(x + (((int64_t)img * h + py) * w + px) * cin + c0 + 4 * q);
-            uint2 u;
-            u.x = f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16);
-            u.y = f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16);
-            *reinterpret_cast<uint2 *>(&Ps[pos * HX_LD + 4 * q]) = u;
-        }
-        // weights of the nine taps: (tap, channel o) rows of 32 k, 4 pieces of 8 each
-        for (int e = tid; e < 9 * BN * 4; e += NT) {
-            const int r = e >> 2, piece = e & 3;
-            const int tap = r / BN, o = r - tap * BN;
-            uint4 u = uint4{0u, 0u, 0u, 0u};
-            if (n0 + o < cout)
-                u = *reinterpret_cast<const uint4 *>(wt + (int64_t)(n0 + o) * K + tap * cin + c0 + 8 * piece);
-            *reinterpret_cast<uint4 *>(&Bs[r * HX_LD + 8 * piece]) = u;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int dy = tap / 3, dx = tap % 3;
-            bf16x8 af[2], bfr[NJ];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                // output pixel (prow, pcol) = (2 wr + i, row) of the patch reads position
-                // (prow + dy, pcol + dx) of the staged patch
-                const int pos = (2 * wr + i + dy) * HX_PW + row + dx;
-                af[i] = as_bf16x8(*reinterpret_cast<const uint4 *>(&Ps[pos * HX_LD + 8 * kq]));
-            }
+        for (int d = 0; d < DEPTH; ++d) {
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                bfr[j] = as_bf16x8(
-                    *reinterpret_cast<const uint4 *>(&Bs[(tap * BN + wc * 16 * NJ + j * 16 + row) * HX_LD + 8 * kq]));
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) acc[i][j] = mma(af[i], bfr[j], acc[i][j]);
+                for (int i = 0; i < MI; ++i) acc[j][i] = mma(as_bf16x8(wv[d][j]), as_bf16x8(av[d][i]), acc[j][i]);
+            IVX_CONV_LOAD(d);
         }
     }
-    // epilogue: D row 4 kq + v is the output pixel (2 wr + i, 4 kq + v) of the patch, column the
-    // channel
+#undef IVX_CONV_LOAD
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i) {
+        const int64_t p = m0 + 16 * i + row;
+        if (p >= P) continue;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int co = n0 + wc * 16 * NJ + j * 16 + row;
-            if (co >= cout) continue;
-            const float bb = bias ? bias[co] : 0.f;
-            const int py = y0 + 2 * wr + i;
+        for (int j = 0; j < NJ; ++j) store_out(out, acc[j][i], p, img[i], py[i], px[i], h, w, cout, n0 + 16 * j + 4 * kq);
+    }
+}
+
+// A block of WM x WN waves owns 2 WM rows x 32 columns of one image and 16 NJ WN output channels.  The
+// patch with its one-pixel halo is staged in LDS once, all input channels of it (the order of the steps
+// runs over channels inside the taps), and serves the nine taps; the weights stay in the vector cache,
+// DEPTH steps ahead (9 cin / 32 steps: DEPTH divides them).  A wave takes 64 pixels x 16 NJ channels: per 32-wide
+// step 4 LDS reads, NJ weight loads, 4 NJ products.  Position rows are padded by 16 bytes, so that eight
+// lanes' reads of consecutive positions cover all banks.
+// Bound by the weight loads and the staging, which the block's own products do not hide (three blocks a CU
+// do): 64 -> 64 channels at 16 x 128^2 in 44 us (440 TFLOP/s), 128 -> 128 at 16 x 64^2 in 31 us (620); staged per
+// chunk and tap from FP32 activations these took 155 and 133 us.  One 256^2 image, whose deep levels
+// are chains of 36 to 108 dependent steps on few blocks: 10 to 20 us a layer, from 47 to 110.
+constexpr int PT_W = 32, PT_PW = PT_W + 2;
+template <typename T, int WM, int WN, int NJ, int DEPTH>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 8))) void
+k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__restrict__ wt, int packed, int cout, int chunks,
+                ConvOut out) {
+    extern __shared__ __align__(16) uint16_t Ps[];
+    constexpr int NTH = 64 * WM * WN, POS = (2 * WM + 2) * PT_PW, U = 8;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kq = lane >> 4, wm = wave % WM, wn = wave / WM;
+    const int tx = (w + PT_W - 1) / PT_W, ty = (h + 2 * WM - 1) / (2 * WM);
+    const int t = blockIdx.x, img = t / (tx * ty), r = t - img * tx * ty;
+    const int y0 = (r / tx) * (2 * WM), x0 = (r % tx) * PT_W;
+    const int n0 = (blockIdx.y * WN + wn) * (16 * NJ);
+    const int K = 9 * cin, ca = in.ca, cb = cin - in.ca, ld = cin + 8;
+    {
+        const int yt = y0 > 0 ? y0 - 1 : 0, sh = in.half0;
+        const int64_t base = (int64_t)img * h * w + (int64_t)yt * w;
+        const int64_t base0 = sh ? ((int64_t)img * (h >> 1) + (yt >> 1)) * (w >> 1) : base;
+        const __amdgpu_buffer_rsrc_t v0 = view(in.x0 + base0 * ca, ((sh ? (int64_t)n * (h >> 1) * (w >> 1) : (int64_t)n * h * w) - base0) * ca * (int)sizeof(T));
+        const __amdgpu_buffer_rsrc_t v1 = view(in.x1 + base * cb, ((int64_t)n * h * w - base) * cb * (int)sizeof(T));
+        // the cs channels of one source, from channel `at0` of the patch on
+        auto stage = [&](const __amdgpu_buffer_rsrc_t &v, int cs, int at0, int sh) {
+            const int pieces = cs / 8;
+            const float inv = 1.f / (float)pieces; // ((e + 1/2) inv is further from an integer than its rounding)
+            for (int e0 = tid; e0 < POS * pieces; e0 += U * NTH) {
+                uint4 q[U];
+                int at[U];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int px = x0 + 4 * kq + v;
-                if (py >= h || px >= w) continue;
-                const int64_t o = (((int64_t)img * h + py) * w + px) * cout + co;
-                float val = acc[i][j][v] + bb;
-                if (relu) val = fmaxf(val, 0.f);
-                if (mask && !(mask[o] > 0.f)) val = 0.f;
-                if (accumulate) val += y[o];
-                y[o] = val;
+                for (int u = 0; u < U; ++u) {
+                    const int e = e0 + u * NTH, pos = (int)(((float)e + 0.5f) * inv), c = 8 * (e - pos * pieces);
+                    const int yy = y0 - 1 + pos / PT_PW, xx = x0 - 1 + pos % PT_PW;
+                    const bool ok = e < POS * pieces && yy >= 0 && yy < h && xx >= 0 && xx < w;
+                    const unsigned p = (unsigned)(((yy >> sh) - (yt >> sh)) * (w >> sh) + (xx >> sh));
+                    at[u] = e < POS * pieces ? pos * ld + at0 + c : POS * ld; // (past the end: a spare piece)
+                    q[u] = load_raw<T>(v, ok ? (p * cs + c) * (unsigned)sizeof(T) : NO_PIECE);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) *reinterpret_cast<uint4 *>(&Ps[at[u]]) = q[u];
             }
+        };
+        stage(v0, ca, 0, sh);
+        if (cb) stage(v1, cb, ca, 0);
+    }
+    const __amdgpu_buffer_rsrc_t rw = view(wt + (int64_t)n0 * K, (int64_t)16 * NJ * K * 2);
+    unsigned wv0[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) wv0[j] = packed ? (unsigned)(16 * j * K + 8 * lane) * 2u : (unsigned)((16 * j + row) * K + 8 * kq) * 2u;
+    // The next step to load: inner and outer position (tap and chunk, or chunk and tap), k in bytes.
+    const int nc = cin / 32, steps = 9 * nc, inner = chunks ? 9 : nc, outer = chunks ? nc : 9;
+    const int dk = chunks ? 2 * cin : 64, back = chunks ? 64 - 16 * cin : 64;
+    int s = 0, so = 0, k2 = 0;
+    u32x4 wv[DEPTH][NJ];
+    int off[DEPTH]; // LDS element offset of the step
+#define IVX_STEP_LOAD(d)                                                                                               \
+    do {                                                                                                               \
+        const bool live = so < outer; /* (steps past the last: the first one's operands, not used) */                  \
+        const int tap = live ? (chunks ? s : so) : 0, ch = live ? (chunks ? so : s) : 0, ky = (tap * 11) >> 5;         \
+        const int kk = __builtin_amdgcn_readfirstlane(live ? k2 << (packed ? 4 : 0) : 0);                              \
+        _Pragma("unroll") for (int j = 0; j < NJ; ++j) wv[d][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, wv0[j], kk, 0); \
+        off[d] = __builtin_amdgcn_readfirstlane((ky * PT_PW + tap - 3 * ky) * ld + 32 * ch);                           \
+        const bool wrap = ++s == inner;                                                                                \
+        s = wrap ? 0 : s;                                                                                              \
+        so += wrap;                                                                                                    \
+        k2 += wrap ? back : dk;                                                                                        \
+    } while (0)
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        IVX_STEP_LOAD(d);
+        __builtin_amdgcn_sched_barrier(0); // (in this order: the loop's waits count them)
+    }
+    f32x4 acc[NJ][4];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint16_t *a0 = Ps + (2 * wm * PT_PW + row) * ld + 8 * kq;
+    auto pixels = [&](int i, int at) {
+        return as_bf16x8(*reinterpret_cast<const uint4 *>(a0 + at + ((i >> 1) * PT_PW + 16 * (i & 1)) * ld));
+    };
+    __syncthreads();
+    bf16x8 a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = pixels(i, 0);
+    for (int s0 = 0; s0 < steps; s0 += DEPTH) { // (9 nc steps: a multiple of DEPTH)
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int next = off[(d + 1) % DEPTH]; // (the slot of step s0 + DEPTH holds it by now)
+            bf16x8 an[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) an[i] = pixels(i, next);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[j][i] = mma(__builtin_bit_cast(bf16x8, wv[d][j]), a[i], acc[j][i]);
+            __builtin_amdgcn_sched_barrier(0); // (the loads of a step stay DEPTH steps ahead of their use)
+            IVX_STEP_LOAD(d);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = an[i];
         }
+    }
+#undef IVX_STEP_LOAD
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int py = y0 + 2 * wm + (i >> 1), px = x0 + 16 * (i & 1) + row;
+        if (py >= h || px >= w) continue;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            store_out(out, acc[j][i], ((int64_t)img * h + py) * w + px, img, py, px, h, w, cout, n0 + 16 * j + 4 * kq);
+    }
 }
 
 // Weight-gradient partials: block (k tile of 64, o tile of 64, pixel range z).
@@ -536,20 +644,193 @@ __global__ __launch_bounds__(NT) void k_conv3x3_gw_tiled(const float *__restrict
     }
 }
 
-// out[i] = sum over splits of part[z][i] in a fixed order: block = 64 consecutive i x 4
-// interleaved split groups, combined in LDS.  i < nw goes to dw, the rest to db.
-__global__ __launch_bounds__(NT) void k_sum_splits(const float *__restrict__ part, int splits, int64_t len,
-                                                   int64_t nw, float *__restrict__ dw, float *__restrict__ db) {
-    __shared__ float sh[4][64];
-    const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-    const int g = threadIdx.x >> 6;
+// Weight and bias gradient partials over 4 x 16 pixel patches: block (c tile of CT channels, o tile of
+// 32, patch range z).  Per patch the block stages dy (64 pixels x 32 o) and x with its one-pixel halo
+// (6 x 18 positions x CT c) in LDS as bf16, once for all nine taps; the operands of a product, whose
+// reduction runs over pixels, are columns of those rows and come through the transposing LDS load
+// (two loads of four consecutive pixels: 32 pixels = two patch rows per product).  A wave owns 16 c x
+// 32 o x 9 taps, 18 products for 22 operand halves.  CT = 64: four c tiles.  CT = 32: two, and waves
+// 2, 3 take the patch's lower two rows (summed over LDS at the end).  Rows are padded by 16 elements, so
+// that the four pixels a 16-lane group reads lie in different banks.
+// Before, each of the nine taps restaged its own shifted view through registers with FP32 rounding:
+// 268 -> 85 us on 32 channels at 256^2 x 16.  part[z] = [dw (cout x K) | db (cout)].
+// Requires cin % 8 == 0 and cout % 8 == 0.
+constexpr int GP_TH = 4, GP_TW = 16, GP_PW = GP_TW + 2, GP_POS = (GP_TH + 2) * GP_PW, GP_OL = 48;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4 read_columns(const uint16_t *at) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
+}
+
+template <typename T, int CT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_conv3x3_gw_patch(ConvIn<T> in, const T *__restrict__ dyb,
+                                                         const float *__restrict__ dy, int n, int h, int w, int cin,
+                                                         int cout, int tiles, int tps, float *__restrict__ part) {
+    constexpr int XL = CT + 16, XPIECES = GP_POS * (CT / 8), XPER = (XPIECES + NT - 1) / NT;
+    __shared__ __align__(16) uint16_t Xs[GP_POS * XL];
+    __shared__ __align__(16) uint16_t Ds[GP_TH * GP_TW * GP_OL];
+    __shared__ float red[CT == 32 ? 2 * 64 * 4 : 1];
+    __shared__ float sb[8][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, g = lane >> 4;
+    const int K = 9 * cin, ca = in.ca, cb = cin - in.ca;
+    const int64_t len = (int64_t)cout * K + cout;
+    const int c0 = blockIdx.x * CT, o0 = blockIdx.y * 32;
+    const int t0 = blockIdx.z * tps, t1 = min(tiles, t0 + tps);
+    const int tx = (w + GP_TW - 1) / GP_TW, ty = (h + GP_TH - 1) / GP_TH;
+    uint4 rx[XPER], rd;
+    float bs[8] = {};
+    const bool do_bias = blockIdx.x == 0;
+    // one 8-channel piece of dy per thread: pixel tid / 4, channels 8 (tid % 4)
+    const int dp = tid >> 2, dc = o0 + 8 * (tid & 3);
+    auto gload = [&](int t) {
+        const int img = t / (tx * ty), r = t - img * tx * ty, y0 = (r / tx) * GP_TH, x0 = (r % tx) * GP_TW;
+        // views of this image: offsets stay small whatever the batch
+        const int64_t base = (int64_t)img * h * w, base0 = in.half0 ? (int64_t)img * (h >> 1) * (w >> 1) : base;
+        {
+            const int yy = y0 + (dp >> 4), xx = x0 + (dp & 15);
+            const bool okp = yy < h && xx < w && dc < cout;
+            const unsigned at = (unsigned)((yy - y0) * w + xx) * cout + dc;
+            const int64_t at0 = (base + (int64_t)y0 * w) * cout, left = ((int64_t)n * h * w * cout - at0);
+            rd = load_raw<T>(view(dyb + at0, left * (int)sizeof(T)), okp ? at * (unsigned)sizeof(T) : NO_PIECE);
+            if (do_bias) {
+                const __amdgpu_buffer_rsrc_t rf = view(dy + at0, left * 4);
+                const f32x4 a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, okp ? 4u * at : NO_PIECE, 0, 0));
+                const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, okp ? 4u * at + 16u : NO_PIECE, 0, 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    bs[e] += a[e];
+                    bs[4 + e] += b[e];
+                }
+            }
+        }
+        const int yt = y0 > 0 ? y0 - 1 : 0, sh0 = in.half0;
+        const int64_t s0 = base0 + (int64_t)(yt >> sh0) * (w >> sh0), s1 = base + (int64_t)yt * w;
+        const __amdgpu_buffer_rsrc_t v0 = view(in.x0 + s0 * ca, ((sh0 ? (int64_t)n * (h >> 1) * (w >> 1) : (int64_t)n * h * w) - s0) * ca * (int)sizeof(T));
+        const __amdgpu_buffer_rsrc_t v1 = view(in.x1 + s1 * cb, ((int64_t)n * h * w - s1) * cb * (int)sizeof(T));
+#pragma unroll
+        for (int u = 0; u < XPER; ++u) {
+            const int e = tid + u * NT, pos = e / (CT / 8), c = c0 + 8 * (e % (CT / 8));
+            const int yy = y0 - 1 + pos / GP_PW, xx = x0 - 1 + pos % GP_PW;
+            const bool okx = e < XPIECES && c < cin && yy >= 0 && yy < h && xx >= 0 && xx < w;
+            const unsigned p0 = (unsigned)(((yy >> sh0) - (yt >> sh0)) * (w >> sh0) + (xx >> sh0)), p1 = (unsigned)((yy - yt) * w + xx);
+            if (c0 < ca) rx[u] = load_raw<T>(v0, okx && c < ca ? (p0 * ca + c) * (unsigned)sizeof(T) : NO_PIECE);
+            else rx[u] = load_raw<T>(v1, okx ? (p1 * cb + (c - ca)) * (unsigned)sizeof(T) : NO_PIECE);
+            if (c0 < ca && c0 + CT > ca && cb) { // (a tile that spans both sources)
+                const uint4 q = load_raw<T>(v1, okx && c >= ca ? (p1 * cb + (c - ca)) * (unsigned)sizeof(T) : NO_PIECE);
+                rx[u] = uint4{rx[u].x | q.x, rx[u].y | q.y, rx[u].z | q.z, rx[u].w | q.w};
+            }
+        }
+    };
+    auto sstore = [&]() {
+        *reinterpret_cast<uint4 *>(&Ds[dp * GP_OL + 8 * (tid & 3)]) = rd;
+#pragma unroll
+        for (int u = 0; u < XPER; ++u) {
+            const int e = tid + u * NT;
+            if (e < XPIECES) *reinterpret_cast<uint4 *>(&Xs[(e / (CT / 8)) * XL + 8 * (e % (CT / 8))]) = rx[u];
+        }
+    };
+    const int cw = CT == 64 ? wave : wave & 1;             // this wave's 16 channels
+    const int r0 = CT == 64 ? 0 : 2 * (wave >> 1), r1 = CT == 64 ? GP_TH : r0 + 2; // and patch rows
+    const bool live = c0 + 16 * cw < cin;
+    f32x4 acc[2][9];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    union Op {
+        s16x4 p[2];
+        bf16x8 v;
+    };
+    // this lane's chunk: pixel 4 g + c16 / 4 of a row, channels 4 (c16 % 4)
+    const int lp = 4 * g + (c16 >> 2), lc = 4 * (c16 & 3);
+    if (t0 < t1) gload(t0);
+    for (int t = t0; t < t1; ++t) {
+        __syncthreads();
+        sstore();
+        __syncthreads();
+        if (t + 1 < t1) gload(t + 1);
+        if (live) {
+            for (int r = r0; r < r1; r += 2) {
+                Op a[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) a[i].p[u] = read_columns(&Ds[((r + u) * GP_TW + lp) * GP_OL + 16 * i + lc]);
+#pragma unroll
+                for (int tap = 0; tap < 9; ++tap) {
+                    Op b;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        b.p[u] = read_columns(&Xs[((r + u + tap / 3) * GP_PW + lp + tap % 3) * XL + 16 * cw + lc]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) acc[i][tap] = mma(a[i].v, b.v, acc[i][tap]);
+                }
+            }
+        }
+    }
+    float *pz = part + (int64_t)blockIdx.z * len;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            if (CT == 32) { // the two halves of the patch
+                __syncthreads();
+                if (wave >= 2) *reinterpret_cast<f32x4 *>(&red[((wave & 1) * 64 + lane) * 4]) = acc[i][tap];
+                __syncthreads();
+                if (wave < 2) acc[i][tap] += *reinterpret_cast<const f32x4 *>(&red[(wave * 64 + lane) * 4]);
+            }
+            const int c = c0 + 16 * cw + c16;
+            if ((CT == 32 && wave >= 2) || c >= cin) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int o = o0 + 16 * i + 4 * g + v;
+                if (o < cout) pz[(int64_t)o * K + tap * cin + c] = acc[i][tap][v];
+            }
+        }
+    if (do_bias) {
+        // sum over the 16 lanes of a wave and the four waves that hold the same channels
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+#pragma unroll
+            for (int q = 4; q < 64; q <<= 1) bs[e] += __shfl_xor(bs[e], q, 64);
+        }
+        __syncthreads();
+        if (lane < 4) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sb[wave][8 * lane + e] = bs[e];
+        }
+        __syncthreads();
+        if (tid < 32 && o0 + tid < cout) pz[(int64_t)cout * K + o0 + tid] = (sb[0][tid] + sb[1][tid]) + (sb[2][tid] + sb[3][tid]);
+    }
+}
+
+// out[i] = sum over splits of part[z][i] in a fixed order: block = 64 consecutive i x 16
+// interleaved split groups, combined in LDS (four groups left the 2,048 splits of the input layer to
+// 19 blocks: 132 us).  i < nw goes to dw, the rest to db.
+__global__ __launch_bounds__(1024) void k_sum_splits(const float *__restrict__ part, int splits, int64_t len,
+                                                     int64_t nw, float *__restrict__ dw, float *__restrict__ db) {
+    __shared__ float sh[16][64];
+    const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + l;
     float s = 0.f;
-    if (i < len)
-        for (int z = g; z < splits; z += 4) s += part[(int64_t)z * len + i];
-    sh[g][threadIdx.x & 63] = s;
+    if (i < len) {
+        int z = g;
+        for (; z + 48 < splits; z += 64) {
+            float t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = part[(int64_t)(z + 16 * u) * len + i];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s += t[u];
+        }
+        for (; z < splits; z += 16) s += part[(int64_t)z * len + i];
+    }
+    sh[g][l] = s;
     __syncthreads();
     if (g == 0 && i < len) {
-        const float t = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; q += 4) t += (sh[q][l] + sh[q + 1][l]) + (sh[q + 2][l] + sh[q + 3][l]);
         if (i < nw) dw[i] = t;
         else db[i - nw] = t;
     }
@@ -592,6 +873,30 @@ __global__ __launch_bounds__(NT) void k_flip(const uint16_t *__restrict__ W, int
     wt[i] = W[((int64_t)o * 9 + (2 - a) * 3 + (2 - b)) * cin + c];
 }
 
+// Place of weight (o, k) of a layer of K = 9 cin.  For cin a multiple of 32 and cout of 16 the network keeps its weights
+// by steps: the 16 channels x 32 k that one product takes are 1 KB in lane order, so that a wave's load
+// is one piece of memory.  From rows of K a load touches 16 rows of 64 bytes, and that
+// bound the convolutions: 64 -> 44 us at 16 x 128^2 x 64 -> 64 channels, 52 -> 31 us at 16 x 64^2 x 128 -> 128.
+// (A weight tensor that a caller passes stays in rows.)
+__host__ __device__ inline int weights_packed(int cin, int cout) { return cin % 32 == 0 && cout % 16 == 0; }
+__device__ __forceinline__ int64_t weight_at(int o, int k, int cin, int cout) {
+    const int K = 9 * cin;
+    if (!weights_packed(cin, cout)) return (int64_t)o * K + k;
+    return ((int64_t)(o >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (o & 15)) * 8 + (k & 7);
+}
+
+// Both bf16 weight sets of a network layer from its master weights [cout][9][cin]: the layer's own and
+// the flipped [cin][9][cout] of its input gradient (there cout is the input count).
+__global__ __launch_bounds__(NT) void k_layer_weights(const float *__restrict__ W, int cin, int cout, uint16_t *__restrict__ wbf,
+                                                      uint16_t *__restrict__ wflip) {
+    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (i >= (int64_t)9 * cin * cout) return;
+    const int c = (int)(i % cin), tap = (int)(i / cin % 9), o = (int)(i / (9 * (int64_t)cin));
+    const uint16_t b = f2bf(W[i]);
+    wbf[weight_at(o, tap * cin + c, cin, cout)] = b;
+    wflip[weight_at(c, (8 - tap) * cout + o, cout, cin)] = b;
+}
+
 __global__ __launch_bounds__(NT) void k_to_bf16(const float *__restrict__ x, int64_t n, uint16_t *__restrict__ y) {
     const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
     if (i < n) y[i] = f2bf(x[i]);
@@ -611,8 +916,27 @@ __global__ __launch_bounds__(NT) void k_pool2(const float *__restrict__ x, int n
     y[i] = fmaxf(fmaxf(b[0], b[c]), fmaxf(b[(int64_t)w * c], b[(int64_t)w * c + c]));
 }
 
+// bf16 activations after a ReLU (non-negative: ordered as integers), eight channels per thread; the
+// rounded maximum is the maximum of the rounded values
+__global__ __launch_bounds__(NT) void k_pool2_bf16(const uint16_t *__restrict__ x, int n, int h, int w, int c,
+                                                   uint16_t *__restrict__ y) {
+    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    const int ho = h / 2, wo = w / 2, c8 = c / 8;
+    if (i >= (int64_t)n * ho * wo * c8) return;
+    const int ch = 8 * (int)(i % c8);
+    const int64_t pix = i / c8;
+    const int xo = (int)(pix % wo), yo = (int)((pix / wo) % ho), nn = (int)(pix / ((int64_t)wo * ho));
+    const uint16_t *b = x + (((int64_t)nn * h + 2 * yo) * w + 2 * xo) * c + ch;
+    typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+    const u16x8 q0 = *reinterpret_cast<const u16x8 *>(b), q1 = *reinterpret_cast<const u16x8 *>(b + c);
+    const u16x8 q2 = *reinterpret_cast<const u16x8 *>(b + (int64_t)w * c), q3 = *reinterpret_cast<const u16x8 *>(b + (int64_t)w * c + c);
+    *reinterpret_cast<u16x8 *>(y + pix * c + ch) = __builtin_elementwise_max(__builtin_elementwise_max(q0, q1), __builtin_elementwise_max(q2, q3));
+}
+
+// dxb (may be NULL): the result rounded to bf16
 __global__ __launch_bounds__(NT) void k_pool2_grad(const float *__restrict__ x, const float *__restrict__ dy, int n,
-                                                   int h, int w, int c, int accumulate, float *__restrict__ dx) {
+                                                   int h, int w, int c, int accumulate, float *__restrict__ dx,
+                                                   uint16_t *__restrict__ dxb) {
     const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
     const int ho = h / 2, wo = w / 2;
     const int64_t tot = (int64_t)n * ho * wo * c;
@@ -631,7 +955,9 @@ __global__ __launch_bounds__(NT) void k_pool2_grad(const float *__restrict__ x, 
             g = dy[i];
             taken = true;
         }
-        dx[off[q]] = accumulate ? dx[off[q]] + g : g;
+        const float v = accumulate ? dx[off[q]] + g : g;
+        dx[off[q]] = v;
+        if (dxb) dxb[off[q]] = f2bf(v);
     }
 }
 
@@ -647,7 +973,7 @@ __global__ __launch_bounds__(NT) void k_up2(const float *__restrict__ x, int n, 
 }
 
 __global__ __launch_bounds__(NT) void k_up2_grad(const float *__restrict__ dy, int n, int h, int w, int c,
-                                                 float *__restrict__ dx) {
+                                                 float *__restrict__ dx, uint16_t *__restrict__ dxb) {
     const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
     const int64_t tot = (int64_t)n * h * w * c;
     if (i >= tot) return;
@@ -656,34 +982,9 @@ __global__ __launch_bounds__(NT) void k_up2_grad(const float *__restrict__ dy, i
     const int xx = (int)(pix % w), yy = (int)((pix / w) % h), nn = (int)(pix / ((int64_t)w * h));
     const int W2 = 2 * w;
     const int64_t b = (((int64_t)nn * 2 * h + 2 * yy) * W2 + 2 * xx) * c + ch;
-    dx[i] = dy[b] + dy[b + c] + dy[b + (int64_t)W2 * c] + dy[b + (int64_t)W2 * c + c];
-}
-
-// out[p] = [a[p] (ca channels), b[p] (cb channels)]
-__global__ __launch_bounds__(NT) void k_concat(const float *__restrict__ a, int ca, const float *__restrict__ b, int cb,
-                                               int64_t P, float *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-    const int c = ca + cb;
-    if (i >= P * c) return;
-    const int ch = (int)(i % c);
-    const int64_t p = i / c;
-    out[i] = ch < ca ? a[p * ca + ch] : b[p * cb + ch - ca];
-}
-
-// da[p] = d[p][:ca]; db[p] (+)= d[p][ca:]
-__global__ __launch_bounds__(NT) void k_split(const float *__restrict__ d, int ca, int cb, int64_t P,
-                                              float *__restrict__ da, float *__restrict__ db, int accumulate_b) {
-    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-    const int c = ca + cb;
-    if (i >= P * c) return;
-    const int ch = (int)(i % c);
-    const int64_t p = i / c;
-    if (ch < ca) {
-        da[p * ca + ch] = d[i];
-    } else {
-        const int64_t o = p * cb + ch - ca;
-        db[o] = accumulate_b ? db[o] + d[i] : d[i];
-    }
+    const float v = dy[b] + dy[b + c] + dy[b + (int64_t)W2 * c] + dy[b + (int64_t)W2 * c + c];
+    dx[i] = v;
+    if (dxb) dxb[i] = f2bf(v);
 }
 
 // network input [n][h][w] -> [n][h][w][4] (channel 0)
@@ -723,7 +1024,8 @@ __global__ __launch_bounds__(NT) void k_head(const float *__restrict__ x, int c,
 constexpr int HEAD_BLOCKS = 512;
 __global__ __launch_bounds__(NT) void k_head_grad(const float *__restrict__ x, int c, int64_t P,
                                                   const float *__restrict__ wt, const float *__restrict__ dy,
-                                                  float *__restrict__ dx, float *__restrict__ part) {
+                                                  float *__restrict__ dx, uint16_t *__restrict__ dxb,
+                                                  float *__restrict__ part) {
     __shared__ float4 sw[NT];
     __shared__ float sb[NT];
     const int G = c >> 2, ppb = NT / G;
@@ -736,9 +1038,11 @@ __global__ __launch_bounds__(NT) void k_head_grad(const float *__restrict__ x, i
         for (int64_t p = (int64_t)blockIdx.x * ppb + lp; p < P; p += (int64_t)gridDim.x * ppb) {
             const float gy = dy[p];
             const float4 v = *reinterpret_cast<const float4 *>(x + p * c + 4 * g);
-            *reinterpret_cast<float4 *>(dx + p * c + 4 * g) =
-                float4{v.x > 0.f ? w4.x * gy : 0.f, v.y > 0.f ? w4.y * gy : 0.f, v.z > 0.f ? w4.z * gy : 0.f,
-                       v.w > 0.f ? w4.w * gy : 0.f};
+            const float4 d = float4{v.x > 0.f ? w4.x * gy : 0.f, v.y > 0.f ? w4.y * gy : 0.f, v.z > 0.f ? w4.z * gy : 0.f,
+                                    v.w > 0.f ? w4.w * gy : 0.f};
+            *reinterpret_cast<float4 *>(dx + p * c + 4 * g) = d;
+            *reinterpret_cast<uint2 *>(dxb + p * c + 4 * g) =
+                uint2{f2bf(d.x) | ((uint32_t)f2bf(d.y) << 16), f2bf(d.z) | ((uint32_t)f2bf(d.w) << 16)};
             a4.x += gy * v.x;
             a4.y += gy * v.y;
             a4.z += gy * v.z;
@@ -832,26 +1136,75 @@ __global__ __launch_bounds__(NT) void k_adam(float *__restrict__ p, const float 
 unsigned nblocks(int64_t n) { return (unsigned)((n + NT - 1) / NT); }
 
 // ------------------------------------------------------------------ launchers
-hipError_t conv3x3(const float *x, int n, int h, int w, int cin, const uint16_t *wt, const float *bias, int cout,
-                   int relu, const float *mask, int accumulate, float *y, hipStream_t st) {
+// 32-bit offsets of a view that starts in the first of so many rows
+bool rows_fit(int rows, int w, int c, size_t size) { return (int64_t)rows * (w + 64) * c * (int64_t)size < (int64_t)1 << 31; }
+
+constexpr size_t LDS_MAX = 160 * 1024;
+size_t patch_lds(int wm, int cin) { return ((size_t)(2 * wm + 2) * PT_PW * (cin + 8) + 8) * sizeof(uint16_t); }
+
+template <typename T, int WM, int WN, int NJ, int DEPTH>
+hipError_t conv3x3_patch(const ConvIn<T> &in, int n, int h, int w, int cin, const uint16_t *wt, int packed, int cout, int chunks,
+                         const ConvOut &out, hipStream_t st) {
+    const size_t lds = patch_lds(WM, cin);
+    const hipError_t e = hipFuncSetAttribute((const void *)k_conv3x3_patch<T, WM, WN, NJ, DEPTH>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+    if (e != hipSuccess) return e;
+    const int64_t tiles = (int64_t)n * ((h + 2 * WM - 1) / (2 * WM)) * ((w + PT_W - 1) / PT_W);
+    k_conv3x3_patch<T, WM, WN, NJ, DEPTH><<<dim3((unsigned)tiles, cout / (16 * NJ * WN)), 64 * WM * WN, lds, st>>>(in, n, h, w, cin, wt, packed, cout, chunks, out);
+    return hipGetLastError();
+}
+
+template <typename T, int MI, int NJ, int DEPTH>
+void conv3x3_wave(const ConvIn<T> &in, int n, int h, int w, int cin, const uint16_t *wt, int packed, int cout, int chunks,
+                  const ConvOut &out, hipStream_t st) {
     const int64_t P = (int64_t)n * h * w;
-    const unsigned gx = (unsigned)((P + 63) / 64);
-    // The halo patch pays where a block covers 32 output channels (measured on the warm-start
-    // network: 197 against 247 us per call); with 64 the tiled kernel is faster (126 against
-    // 141 us), its wider weight tile already amortising the input reads.
-    if (cin % 32 == 0 && cout % 32 == 0 && cout % 64 != 0) {
-        const unsigned gh = (unsigned)((int64_t)n * ((h + HX_TH - 1) / HX_TH) * ((w + HX_TW - 1) / HX_TW));
-        k_conv3x3_halo<1><<<dim3(gh, cout / 32), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask,
-                                                             accumulate, y);
-        return hipGetLastError();
+    const dim3 grid((unsigned)((P + 64 * MI - 1) / (64 * MI)), (unsigned)((cout + 16 * NJ - 1) / (16 * NJ)));
+    if (cin % 32 == 0) k_conv3x3_wave<T, MI, NJ, DEPTH, false><<<grid, NT, 0, st>>>(in, n, h, w, cin, wt, packed, cout, chunks, out);
+    else k_conv3x3_wave<T, MI, NJ, DEPTH, true><<<grid, NT, 0, st>>>(in, n, h, w, cin, wt, packed, cout, chunks, out);
+}
+
+// cin % 8 == 0, cout % 16 == 0.  The output tile of a wave: the largest whose launch still has two
+// waves per SIMD (each halving of the tile doubles the operand loads per product), at smaller problems
+// single 16 x 16 tiles with eight steps in flight.
+template <typename T>
+hipError_t conv3x3(const ConvIn<T> &in, int n, int h, int w, int cin, const uint16_t *wt, int packed, int cout,
+                   const ConvOut &out, hipStream_t st) {
+    // order of the 32-wide steps (fixes the bits of the sums): channel chunks outside the taps where
+    // 32 but not 64 output channels divide, else taps outside
+    const int chunks = cin % 32 == 0 && cout % 32 == 0 && cout % 64 != 0;
+    const int64_t P = (int64_t)n * h * w;
+    auto waves = [&](int mi, int nj) { return ((P + 16 * mi - 1) / (16 * mi)) * ((cout + 16 * nj - 1) / (16 * nj)); };
+    if (cin % 32 == 0 && cout % 32 == 0) {
+        // 64 pixels x 64 (32) channels a wave while that gives the chip's 1,024 SIMDs a wave each (limits of 512 and
+        // 2,048 measure the same within 1%), else 16 channels a wave and nine steps in flight (of four waves'
+        // blocks: one 32^2 image of 256 channels in 14 us, 29 with the large tile's three steps)
+        const bool big = waves(4, cout % 64 == 0 ? 4 : 2) >= 1024;
+#define IVX_PATCH(WM, WN, NJ, DEPTH)                                                                                    \
+    if (patch_lds(WM, cin) <= LDS_MAX && rows_fit(2 * WM + 2, w, cin, sizeof(T)))                                       \
+    return conv3x3_patch<T, WM, WN, NJ, DEPTH>(in, n, h, w, cin, wt, packed, cout, chunks, out, st)
+        if (big && cout % 128 == 0) IVX_PATCH(2, 2, 4, 3);
+        if (big && cout % 64 == 0) IVX_PATCH(4, 1, 4, 3);
+        if (big && cout % 64 != 0) IVX_PATCH(4, 1, 2, 3);
+        if (cout % 64 == 0) IVX_PATCH(1, 4, 1, 9);
+        IVX_PATCH(1, 2, 1, 9);
+#undef IVX_PATCH
     }
-    if (cin >= 16 && cout % 64 == 0)
-        k_conv3x3_tiled<2><<<dim3(gx, cout / 64), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
-    else if (cin >= 16 && cout % 32 == 0)
-        k_conv3x3_tiled<1><<<dim3(gx, cout / 32), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
-    else if (cout % 64 == 0) k_conv3x3<4><<<dim3(gx, cout / 64), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
-    else if (cout % 32 == 0) k_conv3x3<2><<<dim3(gx, cout / 32), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
-    else k_conv3x3<1><<<dim3(gx, (cout + 15) / 16), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
+    constexpr int64_t FULL = 2048;
+    if (cout % 64 == 0 && waves(4, 4) >= FULL) conv3x3_wave<T, 4, 4, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    else if (cout % 32 == 0 && waves(4, 2) >= FULL) conv3x3_wave<T, 4, 2, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    else if (cout % 32 == 0 && waves(2, 2) >= FULL) conv3x3_wave<T, 2, 2, 4>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    else if (waves(4, 1) >= FULL) conv3x3_wave<T, 4, 1, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    else conv3x3_wave<T, 1, 1, 8>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    return hipGetLastError();
+}
+
+// FP32 input of 4, 12, ... channels
+hipError_t conv3x3_narrow(const float *x, int n, int h, int w, int cin, const uint16_t *wt, const float *bias, int cout,
+                          int relu, const float *mask, int accumulate, float *y, uint16_t *yb, hipStream_t st) {
+    const unsigned gx = (unsigned)(((int64_t)n * h * w + 63) / 64);
+    if (cout % 64 == 0) k_conv3x3<4><<<dim3(gx, cout / 64), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
+    else if (cout % 32 == 0) k_conv3x3<2><<<dim3(gx, cout / 32), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
+    else k_conv3x3<1><<<dim3(gx, (cout + 15) / 16), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
     return hipGetLastError();
 }
 
@@ -882,17 +1235,42 @@ int64_t gw_part_len(int n, int h, int w, int cin, int cout) {
     return gw_want_splits(P, cin, cout) * ((int64_t)cout * 9 * cin + cout);
 }
 
+void sum_splits(const float *part, int64_t splits, int cin, int cout, float *dw, float *db, hipStream_t st) {
+    const int64_t nw = (int64_t)cout * 9 * cin, len = nw + cout;
+    k_sum_splits<<<(unsigned)((len + 63) / 64), 1024, 0, st>>>(part, (int)splits, len, nw, dw, db);
+}
+
+bool gw_patch(int cin, int cout) { return cin % 8 == 0 && cout % 8 == 0; }
+
+// Weight and bias gradient over 4 x 16 patches (gw_patch(cin, cout)): dyb is dy as T.  About 1,024
+// blocks (four per compute unit), within the splits the partial buffer is sized for.
+template <typename T>
+hipError_t grad_weight_patch(const ConvIn<T> &in, const T *dyb, const float *dy, int n, int h, int w, int cin, int cout,
+                             float *part, float *dw, float *db, hipStream_t st) {
+    const int ct = cin > 32 ? 64 : 32;
+    const int tiles = n * ((h + GP_TH - 1) / GP_TH) * ((w + GP_TW - 1) / GP_TW);
+    const int gx = (cin + ct - 1) / ct, gy = (cout + 31) / 32;
+    const int64_t most = std::min<int64_t>(gw_want_splits((int64_t)n * h * w, cin, cout), (1024 + gx * gy - 1) / (gx * gy));
+    const int tps = (int)((tiles + most - 1) / most), splits = (tiles + tps - 1) / tps;
+    const dim3 grid(gx, gy, splits);
+    if (ct == 64) k_conv3x3_gw_patch<T, 64><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
+    else k_conv3x3_gw_patch<T, 32><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
+    sum_splits(part, splits, cin, cout, dw, db, st);
+    return hipGetLastError();
+}
+
 hipError_t conv3x3_grad_weight(const float *x, const float *dy, int n, int h, int w, int cin, int cout, float *part,
                                float *dw, float *db, hipStream_t st) {
     const int K = 9 * cin;
+    if (gw_patch(cin, cout) && (int64_t)n * h * w <= INT32_MAX && rows_fit(GP_TH + 2, w, std::max(cin, cout), sizeof(float)))
+        return grad_weight_patch<float>(ConvIn<float>{x, nullptr, cin, 0}, dy, dy, n, h, w, cin, cout, part, dw, db, st);
     if (gw_tiled(cin, cout)) {
         const int64_t P = (int64_t)n * h * w;
         const int64_t ps = gw_split_pixels(P, cin, cout);
         const int64_t splits = (P + ps - 1) / ps;
         k_conv3x3_gw_tiled<<<dim3((K + 63) / 64, (cout + 63) / 64, (unsigned)splits), NT, 0, st>>>(
             x, dy, n, h, w, cin, cout, ps, part);
-        const int64_t len = (int64_t)cout * K + cout;
-        k_sum_splits<<<(unsigned)((len + 63) / 64), NT, 0, st>>>(part, (int)splits, len, (int64_t)cout * K, dw, db);
+        sum_splits(part, splits, cin, cout, dw, db, st);
         return hipGetLastError();
     }
     const int64_t splits = gw_splits(n, h, w);
@@ -941,8 +1319,8 @@ hipError_t scratch_on_current_device(float **out) {
 struct ConvLayer {
     int cin, cout, h, w;       // input channels, output channels, spatial size
     int64_t w_off, b_off;      // offsets into the master parameter vector
-    uint16_t *wbf = nullptr;   // bf16 weights [cout][3][3][cin]
-    uint16_t *wflip = nullptr; // bf16 flipped weights [cin][3][3][cout]
+    uint16_t *wbf = nullptr;   // bf16 weights [cout][3][3][cin], in weight_at's order
+    uint16_t *wflip = nullptr; // bf16 flipped weights [cin][3][3][cout], in weight_at's order
 };
 
 struct ivx_unet {
@@ -953,9 +1331,15 @@ struct ivx_unet {
     int64_t step = 0;
     std::vector<void *> bufs;
     float *params = nullptr, *grads = nullptr, *mom = nullptr, *vel = nullptr;
-    float *xin = nullptr, *xin_grad_dummy = nullptr;
-    std::vector<float *> ea, eb, pool, up, cat, da, db; // forward activations
-    std::vector<float *> g_ea, g_eb, g_pool, g_up, g_cat, g_da, g_db;
+    float *xin = nullptr;
+    // Activations are bf16, as every convolution consumes them; FP32 only where a consumer is not a
+    // convolution: the encoder outputs whose maximum the pooling gradient locates, and the head's input.
+    // Gradients are FP32 (bias sums, pooling and upsampling transposes) with a bf16 copy for the products.
+    std::vector<uint16_t *> ea, ebb, pool, da, dbb;
+    std::vector<float *> eb;
+    float *db0 = nullptr;
+    std::vector<float *> g_ea, g_eb, g_pool, g_up, g_da, g_db;
+    std::vector<uint16_t *> g_eab, g_ebb, g_dab, g_dbb;
     float *out = nullptr, *gout = nullptr;
     float *part = nullptr;
     int64_t part_len = 0;
@@ -993,93 +1377,119 @@ int dec_b(const ivx_unet *u, int l) { return dec_a(u, l) + 1; }
 hipError_t refresh_bf16(ivx_unet *u, hipStream_t st) {
     for (ConvLayer &c : u->conv) {
         const int64_t nw = (int64_t)9 * c.cin * c.cout;
-        k_to_bf16<<<nblocks(nw), NT, 0, st>>>(u->params + c.w_off, nw, c.wbf);
-        k_flip<<<nblocks(nw), NT, 0, st>>>(c.wbf, c.cin, c.cout, c.wflip);
+        k_layer_weights<<<nblocks(nw), NT, 0, st>>>(u->params + c.w_off, c.cin, c.cout, c.wbf, c.wflip);
     }
     return hipGetLastError();
 }
 
-hipError_t forward(ivx_unet *u, const float *x, int B, hipStream_t st) {
+ConvIn<uint16_t> single(const uint16_t *x, int c) { return ConvIn<uint16_t>{x, nullptr, c, 0}; }
+
+// decoder input of level l: the level below upsampled (read at half resolution), then the skip
+ConvIn<uint16_t> dec_in(const ivx_unet *u, int l) {
+    return ConvIn<uint16_t>{l + 1 <= u->L - 2 ? u->dbb[l + 1] : u->ebb[u->L - 1], u->ebb[l], u->ch[l + 1], 1};
+}
+
+// ReLU convolution of the forward pass: bf16 output yb and / or FP32 output y
+hipError_t conv_forward(ivx_unet *u, const ConvLayer &c, int B, const ConvIn<uint16_t> &in, float *y, uint16_t *yb,
+                        hipStream_t st) {
+    ConvOut o{};
+    o.y = y;
+    o.yb = yb;
+    o.bias = u->params + c.b_off;
+    o.relu = 1;
+    return conv3x3<uint16_t>(in, B, c.h, c.w, c.cin, c.wbf, weights_packed(c.cin, c.cout), c.cout, o, st);
+}
+
+// keep: also store the FP32 encoder outputs that the backward pass reads
+hipError_t forward(ivx_unet *u, const float *x, int B, bool keep, hipStream_t st) {
     const int64_t P0 = (int64_t)B * u->H * u->W;
     k_pad_input<<<nblocks(P0), NT, 0, st>>>(x, P0, u->xin);
     hipError_t e;
-    const float *hin = u->xin;
     for (int l = 0; l < u->L; ++l) {
         const int h = lvl_h(u, l), w = lvl_w(u, l);
-        if (l > 0) {
-            const int64_t tot = (int64_t)B * h * w * u->ch[l - 1];
-            k_pool2<<<nblocks(tot), NT, 0, st>>>(u->eb[l - 1], B, 2 * h, 2 * w, u->ch[l - 1], u->pool[l]);
-            hin = u->pool[l];
-        }
         const ConvLayer &a = u->conv[enc_a(l)], &b = u->conv[enc_b(l)];
-        if ((e = conv3x3(hin, B, h, w, a.cin, a.wbf, u->params + a.b_off, a.cout, 1, nullptr, 0, u->ea[l], st)) != hipSuccess) return e;
-        if ((e = conv3x3(u->ea[l], B, h, w, b.cin, b.wbf, u->params + b.b_off, b.cout, 1, nullptr, 0, u->eb[l], st)) != hipSuccess) return e;
+        if (l == 0) {
+            e = conv3x3_narrow(u->xin, B, h, w, a.cin, a.wbf, u->params + a.b_off, a.cout, 1, nullptr, 0, nullptr, u->ea[0], st);
+        } else {
+            k_pool2_bf16<<<nblocks((int64_t)B * h * w * (u->ch[l - 1] / 8)), NT, 0, st>>>(u->ebb[l - 1], B, 2 * h, 2 * w,
+                                                                                          u->ch[l - 1], u->pool[l]);
+            e = conv_forward(u, a, B, single(u->pool[l], a.cin), nullptr, u->ea[l], st);
+        }
+        if (e != hipSuccess) return e;
+        const bool f32 = u->L == 1 || (keep && l < u->L - 1);
+        if ((e = conv_forward(u, b, B, single(u->ea[l], b.cin), f32 ? u->eb[l] : nullptr, u->ebb[l], st)) != hipSuccess) return e;
     }
-    const float *hcur = u->eb[u->L - 1];
     for (int l = u->L - 2; l >= 0; --l) {
-        const int h = lvl_h(u, l), w = lvl_w(u, l);
-        const int64_t P = (int64_t)B * h * w;
-        k_up2<<<nblocks(P * u->ch[l + 1]), NT, 0, st>>>(hcur, B, h / 2, w / 2, u->ch[l + 1], u->up[l]);
-        k_concat<<<nblocks(P * (u->ch[l + 1] + u->ch[l])), NT, 0, st>>>(u->up[l], u->ch[l + 1], u->eb[l], u->ch[l], P, u->cat[l]);
         const ConvLayer &a = u->conv[dec_a(u, l)], &b = u->conv[dec_b(u, l)];
-        if ((e = conv3x3(u->cat[l], B, h, w, a.cin, a.wbf, u->params + a.b_off, a.cout, 1, nullptr, 0, u->da[l], st)) != hipSuccess) return e;
-        if ((e = conv3x3(u->da[l], B, h, w, b.cin, b.wbf, u->params + b.b_off, b.cout, 1, nullptr, 0, u->db[l], st)) != hipSuccess) return e;
-        hcur = u->db[l];
+        if ((e = conv_forward(u, a, B, dec_in(u, l), nullptr, u->da[l], st)) != hipSuccess) return e;
+        if ((e = conv_forward(u, b, B, single(u->da[l], b.cin), l == 0 ? u->db0 : nullptr, l == 0 ? nullptr : u->dbb[l], st)) != hipSuccess) return e;
     }
-    const float *top = u->L > 1 ? u->db[0] : u->eb[0];
+    const float *top = u->L > 1 ? u->db0 : u->eb[0];
     const int hppb = NT / (u->ch[0] / 4);
     k_head<<<(unsigned)((P0 + hppb - 1) / hppb), NT, 0, st>>>(top, u->ch[0], P0, u->params + u->head_w,
                                                             u->params + u->head_b, u->out);
     return hipGetLastError();
 }
 
-// conv layer backward: weight/bias gradients into grads, input gradient (masked by the
-// input activation > 0, accumulated if asked) unless gin is null
-hipError_t conv_backward(ivx_unet *u, const ConvLayer &c, int B, const float *in, const float *gout, float *gin,
-                         int accumulate, hipStream_t st) {
+// conv layer backward: weight/bias gradients into grads, then the input gradient into `o` (masked by
+// the input activation > 0)
+hipError_t conv_backward(ivx_unet *u, const ConvLayer &c, int B, const ConvIn<uint16_t> &in, const float *gout,
+                         const uint16_t *goutb, ConvOut o, hipStream_t st) {
     hipError_t e;
-    if ((e = conv3x3_grad_weight(in, gout, B, c.h, c.w, c.cin, c.cout, u->part, u->grads + c.w_off, u->grads + c.b_off,
-                                 st)) != hipSuccess)
+    if ((e = grad_weight_patch<uint16_t>(in, goutb, gout, B, c.h, c.w, c.cin, c.cout, u->part, u->grads + c.w_off,
+                                         u->grads + c.b_off, st)) != hipSuccess)
         return e;
-    if (gin) return conv3x3(gout, B, c.h, c.w, c.cout, c.wflip, nullptr, c.cin, 0, in, accumulate, gin, st);
-    return hipSuccess;
+    o.maskb = in;
+    return conv3x3<uint16_t>(single(goutb, c.cout), B, c.h, c.w, c.cout, c.wflip, weights_packed(c.cout, c.cin), c.cin, o, st);
 }
 
 hipError_t backward(ivx_unet *u, int B, hipStream_t st) {
     hipError_t e;
     const int64_t P0 = (int64_t)B * u->H * u->W;
-    const float *top = u->L > 1 ? u->db[0] : u->eb[0];
-    float *gtop = u->L > 1 ? u->g_db[0] : u->g_eb[0];
+    const bool flat = u->L == 1;
     const int hppb = NT / (u->ch[0] / 4);
     const unsigned hb = (unsigned)std::min<int64_t>(HEAD_BLOCKS, (P0 + hppb - 1) / hppb);
-    k_head_grad<<<hb, NT, 0, st>>>(top, u->ch[0], P0, u->params + u->head_w, u->gout, gtop, u->head_part);
+    k_head_grad<<<hb, NT, 0, st>>>(flat ? u->eb[0] : u->db0, u->ch[0], P0, u->params + u->head_w, u->gout,
+                                   flat ? u->g_eb[0] : u->g_db[0], flat ? u->g_ebb[0] : u->g_dbb[0], u->head_part);
     k_head_reduce<<<1, NT, 0, st>>>(u->head_part, (int)hb, u->ch[0], u->grads + u->head_w, u->grads + u->head_b);
     // decoder, top level first
     for (int l = 0; l <= u->L - 2; ++l) {
         const int h = lvl_h(u, l), w = lvl_w(u, l);
-        const int64_t P = (int64_t)B * h * w;
         const ConvLayer &a = u->conv[dec_a(u, l)], &b = u->conv[dec_b(u, l)];
-        if ((e = conv_backward(u, b, B, u->da[l], u->g_db[l], u->g_da[l], 0, st)) != hipSuccess) return e;
-        if ((e = conv_backward(u, a, B, u->cat[l], u->g_da[l], u->g_cat[l], 0, st)) != hipSuccess) return e;
+        ConvOut o{};
+        o.y = u->g_da[l];
+        o.yb = u->g_dab[l];
+        if ((e = conv_backward(u, b, B, single(u->da[l], b.cin), u->g_db[l], u->g_dbb[l], o, st)) != hipSuccess) return e;
         // skip half goes to the encoder output of this level, upsampled half to the level below
-        k_split<<<nblocks(P * (u->ch[l + 1] + u->ch[l])), NT, 0, st>>>(u->g_cat[l], u->ch[l + 1], u->ch[l], P,
-                                                                        u->g_up[l], u->g_eb[l], 0);
-        float *below = (l + 1 <= u->L - 2) ? u->g_db[l + 1] : u->g_eb[u->L - 1];
-        k_up2_grad<<<nblocks((int64_t)B * (h / 2) * (w / 2) * u->ch[l + 1]), NT, 0, st>>>(u->g_up[l], B, h / 2, w / 2,
-                                                                                           u->ch[l + 1], below);
+        o = ConvOut{};
+        o.y = u->g_up[l];
+        o.y1 = u->g_eb[l];
+        o.split = u->ch[l + 1];
+        if ((e = conv_backward(u, a, B, dec_in(u, l), u->g_da[l], u->g_dab[l], o, st)) != hipSuccess) return e;
+        const bool mid = l + 1 <= u->L - 2;
+        k_up2_grad<<<nblocks((int64_t)B * (h / 2) * (w / 2) * u->ch[l + 1]), NT, 0, st>>>(
+            u->g_up[l], B, h / 2, w / 2, u->ch[l + 1], mid ? u->g_db[l + 1] : u->g_eb[u->L - 1],
+            mid ? u->g_dbb[l + 1] : u->g_ebb[u->L - 1]);
     }
     // encoder, bottom level first; g_eb[l] for l < L-1 already holds the skip gradient
     for (int l = u->L - 1; l >= 0; --l) {
         const int h = lvl_h(u, l), w = lvl_w(u, l);
         const ConvLayer &a = u->conv[enc_a(l)], &b = u->conv[enc_b(l)];
-        if ((e = conv_backward(u, b, B, u->ea[l], u->g_eb[l], u->g_ea[l], 0, st)) != hipSuccess) return e;
+        ConvOut o{};
+        o.y = u->g_ea[l];
+        o.yb = l > 0 ? u->g_eab[l] : nullptr;
+        if ((e = conv_backward(u, b, B, single(u->ea[l], b.cin), u->g_eb[l], u->g_ebb[l], o, st)) != hipSuccess) return e;
         if (l == 0) {
-            if ((e = conv_backward(u, a, B, u->xin, u->g_ea[l], nullptr, 0, st)) != hipSuccess) return e;
+            if ((e = conv3x3_grad_weight(u->xin, u->g_ea[0], B, h, w, a.cin, a.cout, u->part, u->grads + a.w_off,
+                                         u->grads + a.b_off, st)) != hipSuccess)
+                return e;
         } else {
-            if ((e = conv_backward(u, a, B, u->pool[l], u->g_ea[l], u->g_pool[l], 0, st)) != hipSuccess) return e;
+            o = ConvOut{};
+            o.y = u->g_pool[l];
+            if ((e = conv_backward(u, a, B, single(u->pool[l], a.cin), u->g_ea[l], u->g_eab[l], o, st)) != hipSuccess) return e;
             const int64_t tot = (int64_t)B * h * w * u->ch[l - 1];
             k_pool2_grad<<<nblocks(tot), NT, 0, st>>>(u->eb[l - 1], u->g_pool[l], B, 2 * h, 2 * w, u->ch[l - 1], 1,
-                                                      u->g_eb[l - 1]);
+                                                      u->g_eb[l - 1], u->g_ebb[l - 1]);
         }
     }
     return hipGetLastError();
@@ -1158,26 +1568,28 @@ ivx_status ivx_unet_create(int32_t levels, int32_t base, int32_t max_batch, int3
     }
     const int64_t P0 = B * height * width;
     if ((s = ualloc(u, &u->xin, P0 * 4))) return fail(s);
-    u->ea.resize(levels); u->eb.resize(levels); u->pool.resize(levels); u->up.resize(levels); u->cat.resize(levels);
-    u->da.resize(levels); u->db.resize(levels);
+    u->ea.resize(levels); u->ebb.resize(levels); u->eb.resize(levels); u->pool.resize(levels);
+    u->da.resize(levels); u->dbb.resize(levels);
     u->g_ea.resize(levels); u->g_eb.resize(levels); u->g_pool.resize(levels); u->g_up.resize(levels);
-    u->g_cat.resize(levels); u->g_da.resize(levels); u->g_db.resize(levels);
+    u->g_da.resize(levels); u->g_db.resize(levels);
+    u->g_eab.resize(levels); u->g_ebb.resize(levels); u->g_dab.resize(levels); u->g_dbb.resize(levels);
     int64_t maxpart = 1;
     for (int l = 0; l < levels; ++l) {
         const int64_t P = B * (height >> l) * (width >> l);
         const int c = u->ch[l];
-        if ((s = ualloc(u, &u->ea[l], P * c)) || (s = ualloc(u, &u->eb[l], P * c)) || (s = ualloc(u, &u->g_ea[l], P * c)) ||
-            (s = ualloc(u, &u->g_eb[l], P * c)))
+        if ((s = ualloc(u, &u->ea[l], P * c)) || (s = ualloc(u, &u->ebb[l], P * c)) || (s = ualloc(u, &u->eb[l], P * c)) ||
+            (s = ualloc(u, &u->g_ea[l], P * c)) || (s = ualloc(u, &u->g_eb[l], P * c)) ||
+            (s = ualloc(u, &u->g_eab[l], P * c)) || (s = ualloc(u, &u->g_ebb[l], P * c)))
             return fail(s);
         if (l > 0 && ((s = ualloc(u, &u->pool[l], P * u->ch[l - 1])) || (s = ualloc(u, &u->g_pool[l], P * u->ch[l - 1]))))
             return fail(s);
         if (l <= levels - 2) {
-            const int cc = u->ch[l + 1] + c;
-            if ((s = ualloc(u, &u->up[l], P * u->ch[l + 1])) || (s = ualloc(u, &u->cat[l], P * cc)) ||
-                (s = ualloc(u, &u->da[l], P * c)) || (s = ualloc(u, &u->db[l], P * c)) ||
-                (s = ualloc(u, &u->g_up[l], P * u->ch[l + 1])) || (s = ualloc(u, &u->g_cat[l], P * cc)) ||
-                (s = ualloc(u, &u->g_da[l], P * c)) || (s = ualloc(u, &u->g_db[l], P * c)))
+            if ((s = ualloc(u, &u->da[l], P * c)) || (s = ualloc(u, &u->dbb[l], P * c)) ||
+                (s = ualloc(u, &u->g_up[l], P * u->ch[l + 1])) || (s = ualloc(u, &u->g_da[l], P * c)) ||
+                (s = ualloc(u, &u->g_db[l], P * c)) || (s = ualloc(u, &u->g_dab[l], P * c)) ||
+                (s = ualloc(u, &u->g_dbb[l], P * c)))
                 return fail(s);
+            if (l == 0 && (s = ualloc(u, &u->db0, P * c))) return fail(s);
         }
     }
     for (const ConvLayer &c : u->conv) maxpart = std::max<int64_t>(maxpart, gw_part_len((int)B, c.h, c.w, c.cin, c.cout));
@@ -1237,7 +1649,7 @@ ivx_status ivx_unet_forward(ivx_unet *u, const float *x, float *y, int32_t batch
     if (s) return s;
     if (!x || !y || batch < 1 || batch > u->maxb) return set_error(IVX_EINVAL, "bad forward arguments");
     hipStream_t st = (hipStream_t)stream;
-    UHIP(forward(u, x, batch, st));
+    UHIP(forward(u, x, batch, false, st));
     UHIP(hipMemcpyAsync(y, u->out, (size_t)batch * u->H * u->W * sizeof(float), hipMemcpyDeviceToDevice, st));
     return IVX_OK;
 }
@@ -1248,7 +1660,7 @@ ivx_status ivx_unet_train_step(ivx_unet *u, const float *x, const float *target,
     if (s) return s;
     if (!x || !target || batch < 1 || batch > u->maxb || !(lr > 0.f)) return set_error(IVX_EINVAL, "bad train arguments");
     hipStream_t st = (hipStream_t)stream;
-    UHIP(forward(u, x, batch, st));
+    UHIP(forward(u, x, batch, true, st));
     const int64_t P0 = (int64_t)batch * u->H * u->W;
     k_mse<<<nblocks(P0), NT, 0, st>>>(u->out, target, P0, u->gout, u->loss_part);
     k_sum_double<<<1, NT, 0, st>>>(u->loss_part, (int)nblocks(P0), 1.0 / (double)P0, u->loss);
@@ -1276,7 +1688,7 @@ ivx_status ivx_unet_loss_grad(ivx_unet *u, const float *x, const float *target, 
     if (s) return s;
     if (!x || !target || !grads || batch < 1 || batch > u->maxb) return set_error(IVX_EINVAL, "bad loss_grad arguments");
     hipStream_t st = (hipStream_t)stream;
-    UHIP(forward(u, x, batch, st));
+    UHIP(forward(u, x, batch, true, st));
     const int64_t P0 = (int64_t)batch * u->H * u->W;
     k_mse<<<nblocks(P0), NT, 0, st>>>(u->out, target, P0, u->gout, u->loss_part);
     k_sum_double<<<1, NT, 0, st>>>(u->loss_part, (int)nblocks(P0), 1.0 / (double)P0, u->loss);
@@ -1293,7 +1705,17 @@ ivx_status ivx_nn_conv3x3(const float *x, int32_t n, int32_t h, int32_t w, int32
                           void *stream) {
     if (!x || !weight || !y || n < 1 || h < 1 || w < 1 || cin < 4 || cin % 4 || cout < 16 || cout % 16)
         return set_error(IVX_EINVAL, "bad conv3x3 arguments");
-    UHIP(conv3x3(x, n, h, w, cin, weight, bias, cout, relu, mask, accumulate, y, (hipStream_t)stream));
+    if (cin % 8 == 0 && rows_fit(4, w, cin, sizeof(float))) {
+        ConvOut o{};
+        o.y = y;
+        o.bias = bias;
+        o.relu = relu;
+        o.accumulate = accumulate;
+        o.maskf = mask;
+        UHIP(conv3x3<float>(ConvIn<float>{x, nullptr, cin, 0}, n, h, w, cin, weight, 0, cout, o, (hipStream_t)stream));
+    } else {
+        UHIP(conv3x3_narrow(x, n, h, w, cin, weight, bias, cout, relu, mask, accumulate, y, nullptr, (hipStream_t)stream));
+    }
     return IVX_OK;
 }
 
@@ -1365,7 +1787,7 @@ ivx_status ivx_nn_pool2_grad(const float *x, const float *dy, int32_t n, int32_t
     if (!x || !dy || !dx || n < 1 || h < 2 || w < 2 || h % 2 || w % 2 || c < 1)
         return set_error(IVX_EINVAL, "bad pool2_grad arguments");
     k_pool2_grad<<<nblocks((int64_t)n * (h / 2) * (w / 2) * c), NT, 0, (hipStream_t)stream>>>(x, dy, n, h, w, c,
-                                                                                              accumulate, dx);
+                                                                                              accumulate, dx, nullptr);
     UHIP(hipGetLastError());
     return IVX_OK;
 }
@@ -1379,7 +1801,7 @@ ivx_status ivx_nn_up2(const float *x, int32_t n, int32_t h, int32_t w, int32_t c
 
 ivx_status ivx_nn_up2_grad(const float *dy, int32_t n, int32_t h, int32_t w, int32_t c, float *dx, void *stream) {
     if (!dy || !dx || n < 1 || h < 1 || w < 1 || c < 1) return set_error(IVX_EINVAL, "bad up2_grad arguments");
-    k_up2_grad<<<nblocks((int64_t)n * h * w * c), NT, 0, (hipStream_t)stream>>>(dy, n, h, w, c, dx);
+    k_up2_grad<<<nblocks((int64_t)n * h * w * c), NT, 0, (hipStream_t)stream>>>(dy, n, h, w, c, dx, nullptr);
     UHIP(hipGetLastError());
     return IVX_OK;
 }
