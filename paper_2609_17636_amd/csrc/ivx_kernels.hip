@@ -196,15 +196,18 @@ __global__ __launch_bounds__(NT) void k_col_fwd(Geom g, const cpx *__restrict__ 
 // phi(z) = exp(beta (sqrt(1 - (2z/W)^2) - 1)).  In the float build the exponential is
 // taken as exp2 of a prescaled argument (v_exp_f32, v_sqrt_f32): an argument error d
 // changes phi by phi * d, and phi * |argument| never exceeds 1/e, so the absolute error
-// stays at the rounding level of the peak weight.  beta2 = beta (double build) or
-// beta * log2(e) (float build).
+// stays at the rounding level of the peak weight.  v_sqrt_f32 rounds down on average, which beta makes a
+// common factor of all weights (-1.5e-7 an axis at W = 6, and -3e-7 in the matrix-core gridder's
+// scaling); half the remainder q - s^2, its Newton correction where s is near 1, leaves -1e-8.
+// beta2 = beta (double build) or beta * log2(e) (float build).
 __device__ __forceinline__ real es_kernel(real z, real inv_half_w, real beta2) {
     const real t = z * inv_half_w;
     const real q = real(1) - t * t;
 #ifdef IVX_REAL_DOUBLE
     return exp(beta2 * (sqrt(q > real(0) ? q : real(0)) - real(1)));
 #else
-    return __builtin_amdgcn_exp2f(beta2 * (__builtin_amdgcn_sqrtf(q > 0.f ? q : 0.f) - 1.f));
+    const float p = q > 0.f ? q : 0.f, s = __builtin_amdgcn_sqrtf(p);
+    return __builtin_amdgcn_exp2f(beta2 * __builtin_fmaf(0.5f, __builtin_fmaf(-s, s, p), s - 1.f));
 #endif
 }
 
@@ -432,7 +435,7 @@ __global__ __launch_bounds__(NT) void k_grid(GridArgs a) {
 #ifdef IVX_REAL_DOUBLE
     const real beta2 = g.beta;
 #else
-    const real beta2 = g.beta * 1.4426950408889634f;
+    const real beta2 = (float)g.esc * (0.5f * (float)g.W); // exact (es_shape)
 #endif
     const real zoff = real(0.5) * real(W) - real(1);
     real jacc = real(0);
@@ -911,7 +914,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     for (int i = 0; i < NROW * MX_B; i += 256)
         if (i + 256 <= NROW * MX_B || i + 4 * l < NROW * MX_B) *reinterpret_cast<f32x4 *>(PW + i + 4 * l) = f32x4{0.f, 0.f, 0.f, 0.f};
     const float hw2 = 0.25f * (float)(W * W), zoff = 0.5f * (float)W - 1.f;
-    const float esc = a.esc, esb = a.esb;
+    const float esc = a.esc, esb = a.esb, escw = a.esc / (float)W;
     f32x4 hre = {0.f, 0.f, 0.f, 0.f}, him = {0.f, 0.f, 0.f, 0.f};
     float jacc = 0.f;
     int rbits = 126;              // w r is scaled by 2^rbits
@@ -929,7 +932,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             for (int k = 0; k < (KW > 0 ? KW : 8); ++k) {
                 const float z = zf - (float)k; // exact, and |z| <= W / 2
                 const float t = __builtin_fmaf(-z, z, hw2);
-                float w = __builtin_amdgcn_exp2f(__builtin_fmaf(esc, __builtin_amdgcn_sqrtf(t), -esb));
+                const float s = __builtin_amdgcn_sqrtf(t);
+                float w = __builtin_amdgcn_exp2f(__builtin_fmaf(__builtin_fmaf(-s, s, t), escw, __builtin_fmaf(esc, s, -esb)));
                 if (KW == 0 && k >= W) w = 0.f; // (t may be negative)
                 prow[k * MX_B] = w;
             }
