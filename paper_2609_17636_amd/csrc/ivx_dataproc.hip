@@ -110,8 +110,21 @@ __global__ __launch_bounds__(BT) void k_resample_beam(const real *__restrict__ i
 
 // One thread per (sky pixel, group of MOS_CG channels): per pointing the deprojected position,
 // the bilinear taps and the beam weight are formed once and applied to every channel of the
-// group (the per-channel sums run over the pointings in index order, as before).
-constexpr int MOS_CG = 16;
+// group (the per-channel sums run over the pointings in index order).  Bound by the positions (8
+// bytes a pixel and pointing): MOS_K of them are requested ahead, the beam taps of MOS_K pointings and
+// the image taps of MOS_Q channels together, with clamped addresses instead of a branch around each load.
+// One dependent load after the other took 215 us on 36 pointings of 384^2 x 8 channels, now 164
+// (110 for its bytes at the rate of a copy).
+constexpr int MOS_CG = 16, MOS_K = 4, MOS_Q = 4;
+struct Pair {
+    real a, b;
+};
+// two neighbouring pixels in one load (aligned to a pixel only)
+__device__ __forceinline__ Pair pair(const real *p) {
+    Pair q;
+    __builtin_memcpy(&q, p, sizeof(q));
+    return q;
+}
 __global__ __launch_bounds__(BT) void k_linear_mosaic(int P, int C, int n_sub, const real *__restrict__ sub,
                                                       const real *__restrict__ beams, int N,
                                                       const real *__restrict__ deproj, real pb_min2,
@@ -126,36 +139,74 @@ __global__ __launch_bounds__(BT) void k_linear_mosaic(int P, int C, int n_sub, c
 #pragma unroll
     for (int q = 0; q < MOS_CG; ++q) num[q] = real(0);
     real den = real(0);
-    for (int k = 0; k < P; ++k) {
-        const real row = deproj[((int64_t)k * NN + r) * 2], col = deproj[((int64_t)k * NN + r) * 2 + 1];
-        if (!(row > real(-1) && row < real(n_sub) && col > real(-1) && col < real(n_sub))) continue;
-        const real fr = floor(row), fc = floor(col);
-        const int i0 = (int)fr, j0 = (int)fc;
-        const real fy = row - fr, fx = col - fc;
-        const bool r0 = i0 >= 0, r1 = i0 + 1 < n_sub, q0 = j0 >= 0, q1 = j0 + 1 < n_sub;
-        const real w00 = (r0 && q0) ? (real(1) - fy) * (real(1) - fx) : real(0);
-        const real w01 = (r0 && q1) ? (real(1) - fy) * fx : real(0);
-        const real w10 = (r1 && q0) ? fy * (real(1) - fx) : real(0);
-        const real w11 = (r1 && q1) ? fy * fx : real(0);
-        // clamped tap offsets: a weight is zero wherever its tap is outside
-        const int64_t o00 = (int64_t)max(i0, 0) * n_sub + max(j0, 0);
-        const int64_t o01 = (int64_t)max(i0, 0) * n_sub + min(j0 + 1, n_sub - 1);
-        const int64_t o10 = (int64_t)min(i0 + 1, n_sub - 1) * n_sub + max(j0, 0);
-        const int64_t o11 = (int64_t)min(i0 + 1, n_sub - 1) * n_sub + min(j0 + 1, n_sub - 1);
-        auto tap = [&](const real *img) {
-            return (real(1) - fy) * ((real(1) - fx) * (w00 != real(0) ? img[o00] : real(0)) +
-                                      fx * (w01 != real(0) ? img[o01] : real(0))) +
-                   fy * ((real(1) - fx) * (w10 != real(0) ? img[o10] : real(0)) +
-                         fx * (w11 != real(0) ? img[o11] : real(0)));
-        };
-        const real A = tap(beams + (int64_t)k * n2);
-        if (A == real(0)) continue;
-        const real A2 = A * A;
-        const real *sk = sub + ((int64_t)k * C + c0) * n2;
+    auto positions = [&](int k0, real (&row)[MOS_K], real (&col)[MOS_K]) {
 #pragma unroll
-        for (int q = 0; q < MOS_CG; ++q)
-            if (q < cn) num[q] += A2 * tap(sk + (int64_t)q * n2);
-        den += A2;
+        for (int u = 0; u < MOS_K; ++u) {
+            const int64_t at = ((int64_t)min(k0 + u, P - 1) * NN + r) * 2;
+            row[u] = deproj[at];
+            col[u] = deproj[at + 1];
+        }
+    };
+    real row[MOS_K], col[MOS_K];
+    positions(0, row, col);
+    for (int k0 = 0; k0 < P; k0 += MOS_K) {
+        real fy[MOS_K], fx[MOS_K];
+        Pair beam[MOS_K][2];
+        int64_t o[MOS_K][2]; // the pixel pair of each row
+        unsigned on[MOS_K];  // bit j: tap j lies inside and has weight; 16, 32: both taps are the pair's first, second
+        unsigned any = 0;
+#pragma unroll
+        for (int u = 0; u < MOS_K; ++u) {
+            const bool in = k0 + u < P && row[u] > real(-1) && row[u] < real(n_sub) && col[u] > real(-1) && col[u] < real(n_sub);
+            const real y = in ? row[u] : real(0), x = in ? col[u] : real(0);
+            const real fr = floor(y), fc = floor(x);
+            const int i0 = (int)fr, j0 = (int)fc;
+            fy[u] = y - fr;
+            fx[u] = x - fc;
+            const bool r0 = i0 >= 0, r1 = i0 + 1 < n_sub, q0 = j0 >= 0, q1 = j0 + 1 < n_sub;
+            const real gy = real(1) - fy[u], gx = real(1) - fx[u];
+            on[u] = !in ? 0u
+                        : (r0 && q0 && gy * gx != real(0) ? 1u : 0u) | (r0 && q1 && gy * fx[u] != real(0) ? 2u : 0u) |
+                              (r1 && q0 && fy[u] * gx != real(0) ? 4u : 0u) | (r1 && q1 && fy[u] * fx[u] != real(0) ? 8u : 0u);
+            const int jb = min(max(j0, 0), n_sub - 2);
+            any |= on[u];
+            on[u] |= (j0 < jb ? 16u : 0u) | (j0 > jb ? 32u : 0u);
+            o[u][0] = (int64_t)max(i0, 0) * n_sub + jb;
+            o[u][1] = (int64_t)min(i0 + 1, n_sub - 1) * n_sub + jb;
+        }
+        if (k0 + MOS_K < P) positions(k0 + MOS_K, row, col);
+        if (any == 0) continue;
+#pragma unroll
+        for (int u = 0; u < MOS_K; ++u)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) beam[u][j] = pair(beams + (int64_t)min(k0 + u, P - 1) * n2 + o[u][j]);
+#pragma unroll
+        for (int u = 0; u < MOS_K; ++u) {
+            auto combine = [&](const Pair (&p)[2]) {
+                const real t0 = on[u] & 1u ? (on[u] & 32u ? p[0].b : p[0].a) : real(0);
+                const real t1 = on[u] & 2u ? (on[u] & 16u ? p[0].a : p[0].b) : real(0);
+                const real t2 = on[u] & 4u ? (on[u] & 32u ? p[1].b : p[1].a) : real(0);
+                const real t3 = on[u] & 8u ? (on[u] & 16u ? p[1].a : p[1].b) : real(0);
+                return (real(1) - fy[u]) * ((real(1) - fx[u]) * t0 + fx[u] * t1) + fy[u] * ((real(1) - fx[u]) * t2 + fx[u] * t3);
+            };
+            if ((on[u] & 15u) == 0) continue;
+            const real A = combine(beam[u]);
+            if (A == real(0)) continue;
+            const real A2 = A * A;
+            const real *sk = sub + ((int64_t)(k0 + u) * C + c0) * n2;
+#pragma unroll
+            for (int q0 = 0; q0 < MOS_CG; q0 += MOS_Q) {
+                if (q0 >= cn) break;
+                Pair t[MOS_Q][2];
+#pragma unroll
+                for (int q = 0; q < MOS_Q; ++q)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) t[q][j] = pair(sk + (int64_t)min(q0 + q, cn - 1) * n2 + o[u][j]);
+#pragma unroll
+                for (int q = 0; q < MOS_Q; ++q) num[q0 + q] += A2 * combine(t[q]);
+            }
+            den += A2;
+        }
     }
     const bool keep = den > real(0) && den >= pb_min2;
 #pragma unroll

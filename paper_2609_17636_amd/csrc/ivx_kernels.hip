@@ -1873,9 +1873,19 @@ __global__ __launch_bounds__(NT) void k_feather_cols(cpx *__restrict__ work, dou
     __shared__ cpx tws[tw_len<LOGN>()];
     const int c = blockIdx.y, c0 = blockIdx.x * CB;
     cpx *Wc = work + (int64_t)c * N * RW;
-    for (int e = threadIdx.x; e < N * CB; e += NT) {
-        const int q = e / CB, cc = e - q * CB;
-        buf[fft_at<LOGN, CB>(q, cc)] = c0 + cc < RW ? Wc[(int64_t)q * RW + c0 + cc] : cpx{0, 0};
+    // (COL_LOADS rows in flight, columns past the end read element 0: 57 -> 42 us at 8 x 1024^2, 14 for its bytes)
+    for (int e0 = threadIdx.x; e0 < N * CB; e0 += COL_LOADS * NT) {
+        cpx v[COL_LOADS];
+#pragma unroll
+        for (int u = 0; u < COL_LOADS; ++u) {
+            const int e = e0 + u * NT, q = e / CB, cc = e - q * CB;
+            v[u] = Wc[e < N * CB && c0 + cc < RW ? (int64_t)q * RW + c0 + cc : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < COL_LOADS; ++u) {
+            const int e = e0 + u * NT, q = e / CB, cc = e - q * CB;
+            if (e < N * CB) buf[fft_at<LOGN, CB>(q, cc)] = c0 + cc < RW ? v[u] : cpx{0, 0};
+        }
     }
     tw_fill<LOGN>(tws);
     __syncthreads();
