@@ -312,7 +312,9 @@ __global__ __launch_bounds__(NT) void k_cp_q(const double *__restrict__ skey, co
 }
 
 // ------------------------------------------------------------------ scans
-// Exclusive prefix sums along each row of a [rows][L] array, three passes, fixed order.
+// Exclusive prefix sums along each row of a [rows][L] array, three passes, fixed order.  An entry's sum
+// takes the entries before it and nothing else (no subtraction of a later-summed total): the walk over a
+// prefix of the breakpoints then has the bits of the walk over all of them.
 __device__ __forceinline__ double block_exscan(double v, double &total) {
     __shared__ double sh[NT / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -330,7 +332,8 @@ __device__ __forceinline__ double block_exscan(double v, double &total) {
         total += sh[w];
     }
     __syncthreads();
-    return base + inc - v;
+    const double before = __shfl_up(inc, 1);
+    return lane > 0 ? base + before : base;
 }
 
 __global__ __launch_bounds__(NT) void k_scan_sums(const double *__restrict__ in, int64_t L, int nb,
