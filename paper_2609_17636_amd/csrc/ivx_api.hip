@@ -427,9 +427,21 @@ ivx_status apply_geometry(ivx_plan *p, int W, int nf) {
     return IVX_OK;
 }
 
-// Default blocking: the widest block (4 waves) and a 16-cell tile when they fit the LDS
-// budget, else fewer waves, else other tile edges.  ivx_autotune refines it by timing.
+// Default blocking.  Float plans of kernels up to 8 cells: the matrix-core gridder at its largest tile
+// (window 16), which is the faster one over the whole range: against the vector gridder's default 86 : 162 us
+// (six pointings of 150^2 and 157,000 visibilities, forward and adjoint), 341 : 1194 (15 x 112^2 x
+// 1,067,000), 116 : 229 (one 64^2 field of 1,000,000), 72 : 77 (256^2 of 3,000) and within the runs'
+// spread at the smallest (64^2 of 20,000: 71 : 71).  Its windows take up to 1.5 times the memory.  Otherwise the vector
+// gridder: the widest block (4 waves) and a 16-cell tile when they fit the LDS budget, else fewer
+// waves, else other tile edges.  ivx_autotune refines it by timing.
 bool auto_blocking(ivx_plan *p) {
+    if (tile_fits(p, 17 - p->g.W, 1, GRID_MFMA_LANES)) {
+        p->nwave = 1;
+        p->lanes = GRID_MFMA_LANES;
+        p->vpi = 1;
+        set_tile(p, 17 - p->g.W);
+        return true;
+    }
     const int waves[] = {4, 2, 1};
     const int cand[] = {16, 24, 12, 32, 8};
     for (int nw : waves)
