@@ -1678,7 +1678,7 @@ ivx_status set_data_impl(ivx_plan *p, const VisSource &src, bool shared, const i
     // ---- single dish
     if (sd_active(p)) {
         const int sdn = p->d.sd_n;
-        p->n_kpart = (int)(((int64_t)g.C * sdn * sdn + 255) / 256);
+        p->n_kpart = sd_col_blocks(g, sdn);
         if ((s = dalloc(p, &p->d_sdmap, h_sd.size())) != IVX_OK) goto fail_free;
         if ((s = dalloc(p, &p->d_gB, p->gB_host.size())) != IVX_OK) goto fail_free;
         if ((s = dalloc(p, &p->d_U, (size_t)g.C * g.N * sdn)) != IVX_OK) goto fail_free;

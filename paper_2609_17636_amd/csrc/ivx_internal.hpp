@@ -140,6 +140,7 @@ hipError_t launch_row_inv(const Geom &g, const cpx *R, const real *beams, const 
                           const real *dq, const cpx *tw, real *gp, hipStream_t st);
 hipError_t launch_sd_rows(const Geom &g, const real *sky, const real *gB, int rb, int sd_n,
                           int stride, int offset, real *U, hipStream_t st);
+int sd_col_blocks(const Geom &g, int sd_n); // partial sums of the single-dish term
 hipError_t launch_sd_cols(const Geom &g, const real *U, const real *gB, int rb, int sd_n,
                           int stride, int offset, const real *sdmap, real inv_var, real *E,
                           double *kpart, hipStream_t st);
