@@ -432,8 +432,11 @@ ivx_status apply_geometry(ivx_plan *p, int W, int nf) {
 // (six pointings of 150^2 and 157,000 visibilities, forward and adjoint), 341 : 1194 (15 x 112^2 x
 // 1,067,000), 116 : 229 (one 64^2 field of 1,000,000), 72 : 77 (256^2 of 3,000) and within the runs'
 // spread at the smallest (64^2 of 20,000: 71 : 71).  Its windows take up to 1.5 times the memory.  Otherwise the vector
-// gridder: the widest block (4 waves) and a 16-cell tile when they fit the LDS budget, else fewer
-// waves, else other tile edges.  ivx_autotune refines it by timing.
+// gridder: the widest block (4 waves) and a 16-cell tile when they fit the LDS budget, else 2 waves, else
+// other tile edges.  Where only one wave fits (double plans of 13-cell kernels and more) the smallest
+// tile: its blocks are the ones of which most fit a compute unit, and nothing is shared between waves
+// (nine 128^2 pointings of 200,000 visibilities 1088 us in 16-cell tiles, 817 in 13; 512^2 of 630,000 467 : 367;
+// 64^2 of 900 101 : 95).  ivx_autotune refines it by timing.
 bool auto_blocking(ivx_plan *p) {
     if (tile_fits(p, 17 - p->g.W, 1, GRID_MFMA_LANES)) {
         p->nwave = 1;
@@ -442,7 +445,7 @@ bool auto_blocking(ivx_plan *p) {
         set_tile(p, 17 - p->g.W);
         return true;
     }
-    const int waves[] = {4, 2, 1};
+    const int waves[] = {4, 2};
     const int cand[] = {16, 24, 12, 32, 8};
     for (int nw : waves)
         for (int T : cand)
@@ -452,6 +455,13 @@ bool auto_blocking(ivx_plan *p) {
                 set_tile(p, T);
                 return true;
             }
+    for (int T = p->g.W; T <= 32; ++T)
+        if (tile_fits(p, T, 1, 16)) {
+            p->nwave = 1;
+            p->lanes = 16;
+            set_tile(p, T);
+            return true;
+        }
     return false;
 }
 
