@@ -695,7 +695,10 @@ int grid_groups_per_wave(int W, int lanes) { return (lanes == 8 && W <= 8) ? 8 :
 // (m = l % 32, axis l / 32), stored to a row of LDS between zeros that are never overwritten, and
 // read back at the window's fixed positions as a row shifted by the footprint's start: no
 // per-batch clearing and no test of the footprint's bounds.  The K = m operands of the spread are
-// rows [m][position] read through the transposing LDS load.
+// rows [m][position] read through the transposing LDS load.  About 165 vector instructions and 9 matrix
+// instructions a batch at W = 7, 1,150 cycles of a SIMD.  Measured against FP32 matrix products in batches
+// of 16 (950 cycles each): 790 -> 450 us on 34 M visibilities of 36 pointings, 7.8 -> 5.2 ms on
+// eight channels of them, 28 -> 19 us on one 512^2 pointing of 630,000.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -1053,11 +1056,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 
 // ----------------------------------------------------------------------- fold
 // Two passes.  (1) k_ext_sum: the adjoint extended grid E = sum of every work item's
-// window placed at its tile, computed owner-wise: the block of (virtual) tile (vy, vx)
-// owns the T x T cells starting at (vy T, vx T), which only the windows of tiles
-// (vy - dy, vx - dx), dy, dx in {0, 1}, reach (a window spans T + W - 1 <= 2T cells);
-// their slot lists are uniform per block and the window reads are contiguous along
-// rows.  E overwrites the forward extended grid, which the gridding pass has consumed.
+// window placed at its tile, computed owner-wise: the T x T cells starting at (vy T, vx T), those
+// of the (virtual) tile (vy, vx), are reached only by the windows of tiles
+// (vy - dy, vx - dx), dy, dx in {0, 1} (a window spans T + W - 1 <= 2T cells), and the window
+// reads are contiguous along rows.  E overwrites the forward extended grid, which the gridding pass has consumed.
 // (2) in the adjoint column pass, every half-plane cell sums the extended-grid cells that
 // alias to it (periodic rows and columns) and is symmetrised, Hs = (H(t) + conj H(-t)) / 2,
 // as it is loaded for the inverse column FFT.
