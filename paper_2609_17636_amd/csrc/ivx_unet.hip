@@ -1349,6 +1349,33 @@ struct ivx_unet {
 
 namespace {
 
+// Normal deviates by the polar method (Marsaglia and Bray 1964): the values that
+// std::normal_distribution gives here for the same generator, without its extended-precision unit interval, which
+// made 75 to 130 ms of a network's creation (4 levels of base 32; now 20).
+struct Normal {
+    std::mt19937_64 &rng;
+    double sd, spare = 0.0;
+    bool have = false;
+    Normal(std::mt19937_64 &r, double s) : rng(r), sd(s) {}
+    double unit() { return std::min((double)rng() * 5.42101086242752217e-20, 1.0 - 1.11022302462515654e-16); } // 2^-64
+    double operator()() {
+        if (have) {
+            have = false;
+            return spare * sd;
+        }
+        double x, y, r2;
+        do {
+            x = 2.0 * unit() - 1.0;
+            y = 2.0 * unit() - 1.0;
+            r2 = x * x + y * y;
+        } while (r2 > 1.0 || r2 == 0.0);
+        const double m = std::sqrt(-2.0 * std::log(r2) / r2);
+        spare = x * m;
+        have = true;
+        return y * m * sd;
+    }
+};
+
 template <typename T> ivx_status ualloc(ivx_unet *u, T **p, int64_t count) {
     void *q = nullptr;
     if (hipMalloc(&q, (size_t)(count > 0 ? count : 1) * sizeof(T)) != hipSuccess) {
@@ -1602,12 +1629,12 @@ ivx_status ivx_unet_create(int32_t levels, int32_t base, int32_t max_batch, int3
     std::vector<float> h(off, 0.f);
     std::mt19937_64 rng(seed);
     for (const ConvLayer &c : u->conv) {
-        std::normal_distribution<double> nd(0.0, std::sqrt(2.0 / (9.0 * c.cin)));
-        for (int64_t i = 0; i < (int64_t)9 * c.cin * c.cout; ++i) h[c.w_off + i] = (float)nd(rng);
+        Normal nd(rng, std::sqrt(2.0 / (9.0 * c.cin)));
+        for (int64_t i = 0; i < (int64_t)9 * c.cin * c.cout; ++i) h[c.w_off + i] = (float)nd();
     }
     {
-        std::normal_distribution<double> nd(0.0, std::sqrt(1.0 / u->ch[0]));
-        for (int k = 0; k < u->ch[0]; ++k) h[u->head_w + k] = (float)nd(rng);
+        Normal nd(rng, std::sqrt(1.0 / u->ch[0]));
+        for (int k = 0; k < u->ch[0]; ++k) h[u->head_w + k] = (float)nd();
     }
     if ((s = ivx_unet_set_params(u, h.data())) != IVX_OK) return fail(s);
     *out = u;
