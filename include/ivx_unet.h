@@ -3,9 +3,9 @@
  * et al. 2015) mapping the normalised dirty mosaic d = -grad Q(0) / max|d| to an initial
  * sky x0 / 50 K, trained on converged cold-start solutions of the same objective.  All
  * layers run in hand-written gfx950 kernels: 3x3 convolutions as implicit GEMMs on the
- * bf16 matrix cores (v_mfma_f32_16x16x16_bf16) with bf16 weights and activations rounded
- * to bf16 on load, FP32 accumulation and FP32 master weights; pooling, nearest upsampling,
- * concatenation, ReLU, the 1x1 head, MSE and Adam in FP32 vector code.
+ * bf16 matrix cores (v_mfma_f32_16x16x32_bf16) with bf16 weights and activations (rounded once,
+ * as a network stores them; on load in the single-layer calls), FP32 accumulation and FP32 master
+ * weights; pooling gradients, ReLU, the 1x1 head, MSE and Adam in FP32 vector code.
  *
  * Layouts: activations NHWC float ([n][y][x][c]); 3x3 weights [out][3][3][in] (bf16 bits
  * as uint16 where noted); the network input and output are [batch][height][width] float

@@ -696,7 +696,7 @@ int grid_groups_per_wave(int W, int lanes) { return (lanes == 8 && W <= 8) ? 8 :
 // read back at the window's fixed positions as a row shifted by the footprint's start: no
 // per-batch clearing and no test of the footprint's bounds.  The K = m operands of the spread are
 // rows [m][position] read through the transposing LDS load.  About 165 vector instructions and 9 matrix
-// instructions a batch at W = 7, 1,150 cycles of a SIMD.  Measured against FP32 matrix products in batches
+// instructions a batch at W = 7, 883 cycles of a SIMD with a work item's share.  Measured against FP32 matrix products in batches
 // of 16 (950 cycles each): 790 -> 450 us on 34 M visibilities of 36 pointings, 7.8 -> 5.2 ms on
 // eight channels of them, 28 -> 19 us on one 512^2 pointing of 630,000.
 typedef float f32x4 __attribute__((ext_vector_type(4)));

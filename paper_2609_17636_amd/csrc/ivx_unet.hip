@@ -1146,9 +1146,11 @@ template <typename T, int WM, int WN, int NJ, int DEPTH>
 hipError_t conv3x3_patch(const ConvIn<T> &in, int n, int h, int w, int cin, const uint16_t *wt, int packed, int cout, int chunks,
                          const ConvOut &out, hipStream_t st) {
     const size_t lds = patch_lds(WM, cin);
-    const hipError_t e = hipFuncSetAttribute((const void *)k_conv3x3_patch<T, WM, WN, NJ, DEPTH>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
-    if (e != hipSuccess) return e;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k_conv3x3_patch<T, WM, WN, NJ, DEPTH>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+        if (e != hipSuccess) return e;
+    }
     const int64_t tiles = (int64_t)n * ((h + 2 * WM - 1) / (2 * WM)) * ((w + PT_W - 1) / PT_W);
     k_conv3x3_patch<T, WM, WN, NJ, DEPTH><<<dim3((unsigned)tiles, cout / (16 * NJ * WN)), 64 * WM * WN, lds, st>>>(in, n, h, w, cin, wt, packed, cout, chunks, out);
     return hipGetLastError();
