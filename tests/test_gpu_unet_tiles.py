@@ -76,3 +76,19 @@ def test_network_tiles(nn, levels, base, batch, h, w):
         k = int(np.prod(shp)) if shp else 1
         assert np.linalg.norm(g[o:o + k] - wg[o:o + k]) <= 2e-2 * np.linalg.norm(wg[o:o + k]), name
         o += k
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [(1, 1, 1, 40, 64), (2, 5, 17, 64, 64), (1, 9, 31, 72, 128), (3, 4, 16, 40, 96),
+                                            (1, 13, 19, 32, 64), (2, 6, 7, 8, 24)])
+def test_conv3x3_grad_weight_tiles(nn, n, h, w, cin, cout):
+    rng = np.random.default_rng(cin + cout + h)
+    x = rng.standard_normal((n, h, w, cin)).astype(np.float32)
+    dy = rng.standard_normal((n, h, w, cout)).astype(np.float32)
+    dw, db = nn.conv3x3_grad_weight(_dev(x), _dev(dy))
+    qx, qy = U.bf16(x), U.bf16(dy)
+    want = U.conv3x3_grad_weight(qx, qy)[0]
+    size = U.conv3x3_grad_weight(np.abs(qx), np.abs(qy))[0]
+    P = n * h * w  # products of a weight's sum, and a few additions of partial sums
+    assert np.all(np.abs(dw.cpu().numpy() - want) <= (P + 8) * U24 * size + 1e-30)
+    s = dy.astype(np.float64).sum(axis=(0, 1, 2))
+    assert np.all(np.abs(db.cpu().numpy() - s) <= (P + 8) * U24 * np.abs(dy).sum(axis=(0, 1, 2)))
