@@ -18,12 +18,21 @@ __device__ __forceinline__ cpx csub(cpx a, cpx b) { return cpx{a.re - b.re, a.im
 
 // ------------------------------------------------------------------------------ FFT
 // In-LDS Stockham autosort FFT of CB transforms of length N = 2^LOGN in place: element i of
-// transform c is buf[fft_at<LOGN, CB>(i, c)].  The stages (radix 2 first when LOGN is odd, then
-// radix 4) run two at a time in registers, 16 (or 8) points a thread, so that a 1024-point
-// transform passes through LDS three times instead of five (forward column pass of 36 images of
-// 1024-point columns: 94 -> 74 us, 45 for its bytes at the rate of a copy).  Twiddles come from a table
-// tw[t] = exp(-2 pi i t / N), t < 3N/4, staged in LDS through TwStage (conjugated for the inverse);
-// no scaling is applied in either direction.
+// transform c is buf[Fft<LOGN, CB, PAIR>::at(i, c)].  The stages are radix 2 first when LOGN is odd, then
+// radix 4.  Each reads all of a thread's inputs into registers, synchronises, then writes the
+// outputs.  Twiddles come from a table tw[t] = exp(-2 pi i t / N), t < 3N/4, staged in LDS through
+// TwStage (conjugated for the inverse); no scaling is applied in either direction.
+//
+// PAIR runs the stages two at a time in registers, 16 (or 8) points a thread, so that a 1024-point
+// transform passes through LDS three times instead of five, at a quarter of the threads.  Both forms
+// do the same operations on the same values.  Each kernel takes the one that measured faster (single :
+// paired, us, 36 images of 1024-point columns unless stated):
+//   forward columns 91 : 80, inverse rows 34 : 30, plane passes of the full model 315 : 292 together
+//   image rows 44.6 : 47.2 (cube of 128 channels 4,240 : 4,540); at 2048 points 13.9 : 12.0
+//   fold + inverse columns 198 : 207 (cube 19,150 : 20,400): bound by its slot loads, whose
+//   threads a paired stage leaves idle
+//   one column a block of one 1024-point image: the same; of the double build 27.3 : 24.6
+// Below 1024 points a block pairing leaves less than a wave at work (4 of the 70 us of a 64^2 field).
 template <int LOGN> constexpr int tw_len() { return 3 * (1 << LOGN) / 4; }
 
 // The twiddle table is fetched into registers at the start of a kernel and stored to LDS
@@ -48,14 +57,12 @@ template <int LOGN> struct TwStage {
     }
 };
 
-// Place of element i of transform c.  The low four bits are xored with the next four: the outputs
+// Paired stages: the low four bits of an index are xored with the next four, since the outputs
 // of a 16-point thread at the first stages are 16 elements apart from lane to lane, which without it
 // meet in one bank.  Transforms are N + 16 apart, so that lanes that walk c and lanes that walk i
-// both spread over the banks.
+// both spread over the banks.  Single stages: transforms interleaved.
 __device__ __forceinline__ int fft_swz(int i) { return i ^ ((i >> 4) & 15); }
 template <int LOGN, int CB> constexpr int fft_ld() { return CB > 1 ? (1 << LOGN) + 16 : 1 << LOGN; }
-template <int LOGN, int CB> constexpr int fft_len() { return CB * fft_ld<LOGN, CB>(); }
-template <int LOGN, int CB> __device__ __forceinline__ int fft_at(int i, int c) { return c * fft_ld<LOGN, CB>() + fft_swz(i); }
 
 // (a0, a1, a2, a3) -> their 4-point transform in place
 template <bool INV> __device__ __forceinline__ void radix4(cpx &a0, cpx &a1, cpx &a2, cpx &a3) {
@@ -135,22 +142,110 @@ __device__ __forceinline__ void fft_pass(cpx *buf, const cpx *tw) {
     __syncthreads();
 }
 
-// Stages are paired where that leaves a wave of threads at work (CB N / 16 >= 64): a 128-point row
-// on 8 threads is a longer chain than on 32 (4 us of the 70 of a 64^2 field's evaluation).
-template <int LOGN, int CB, bool INV, int NS = 1> __device__ __forceinline__ void fft_lds(cpx *buf, const cpx *tw) {
+template <int LOGN, int CB, bool INV, int NS = 1> __device__ __forceinline__ void fft_paired(cpx *buf, const cpx *tw) {
     constexpr int N = 1 << LOGN;
-    constexpr bool PAIR = CB * N >= 1024;
     if constexpr (NS == 1 && (LOGN & 1)) {
-        fft_pass<LOGN, CB, INV, NS, 2, PAIR>(buf, tw);
-        fft_lds<LOGN, CB, INV, PAIR ? 8 : 2>(buf, tw);
-    } else if constexpr (PAIR && N / NS >= 16) {
+        fft_pass<LOGN, CB, INV, NS, 2, true>(buf, tw);
+        fft_paired<LOGN, CB, INV, 8>(buf, tw);
+    } else if constexpr (N / NS >= 16) {
         fft_pass<LOGN, CB, INV, NS, 4, true>(buf, tw);
-        fft_lds<LOGN, CB, INV, 16 * NS>(buf, tw);
+        fft_paired<LOGN, CB, INV, 16 * NS>(buf, tw);
     } else if constexpr (N / NS >= 4) {
         fft_pass<LOGN, CB, INV, NS, 4, false>(buf, tw);
-        fft_lds<LOGN, CB, INV, 4 * NS>(buf, tw);
+        fft_paired<LOGN, CB, INV, 4 * NS>(buf, tw);
     }
 }
+
+template <int LOGN, int CB, bool INV> __device__ __forceinline__ void fft_single(cpx *buf, const cpx *tw) {
+    constexpr int N = 1 << LOGN;
+    const int tid = threadIdx.x;
+    int Ns = 1;
+    if constexpr (LOGN & 1) {
+        constexpr int TOT = CB * (N / 2);
+        constexpr int BPT = (TOT + NT - 1) / NT;
+        cpx v0[BPT], v1[BPT];
+#pragma unroll
+        for (int t = 0; t < BPT; ++t) {
+            const int u = tid + t * NT;
+            if (u < TOT) {
+                const int c = u % CB, jj = u / CB;
+                v0[t] = buf[jj * CB + c];
+                v1[t] = buf[(jj + N / 2) * CB + c];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < BPT; ++t) {
+            const int u = tid + t * NT;
+            if (u < TOT) {
+                const int c = u % CB, jj = u / CB;
+                buf[(2 * jj) * CB + c] = cadd(v0[t], v1[t]);
+                buf[(2 * jj + 1) * CB + c] = csub(v0[t], v1[t]);
+            }
+        }
+        __syncthreads();
+        Ns = 2;
+    }
+#pragma unroll
+    for (int s = 0; s < LOGN / 2; ++s) {
+        constexpr int TOT = CB * (N / 4);
+        constexpr int BPT = (TOT + NT - 1) / NT;
+        cpx v[BPT][4];
+        const int st = N / (4 * Ns);
+#pragma unroll
+        for (int t = 0; t < BPT; ++t) {
+            const int u = tid + t * NT;
+            if (u < TOT) {
+                const int c = u % CB, jj = u / CB;
+                const int k = jj & (Ns - 1);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    cpx x = buf[(jj + r * (N / 4)) * CB + c];
+                    if (r > 0) {
+                        cpx w = tw[k * r * st];
+                        if (INV) w.im = -w.im;
+                        x = cmul(x, w);
+                    }
+                    v[t][r] = x;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < BPT; ++t) {
+            const int u = tid + t * NT;
+            if (u < TOT) {
+                const int c = u % CB, jj = u / CB;
+                const int k = jj & (Ns - 1);
+                radix4<INV>(v[t][0], v[t][1], v[t][2], v[t][3]);
+                const int o = ((jj - k) << 2) + k;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) buf[(o + r * Ns) * CB + c] = v[t][r];
+            }
+        }
+        __syncthreads();
+        Ns *= 4;
+    }
+}
+
+template <int LOGN, int CB, bool PAIR> struct Fft {
+    static constexpr int LEN = PAIR ? CB * fft_ld<LOGN, CB>() : CB << LOGN;
+    static __device__ __forceinline__ int at(int i, int c = 0) {
+        return PAIR ? c * fft_ld<LOGN, CB>() + fft_swz(i) : i * CB + c;
+    }
+    static __device__ __forceinline__ void forward(cpx *buf, const cpx *tw) {
+        if constexpr (PAIR) fft_paired<LOGN, CB, false>(buf, tw);
+        else fft_single<LOGN, CB, false>(buf, tw);
+    }
+    static __device__ __forceinline__ void inverse(cpx *buf, const cpx *tw) {
+        if constexpr (PAIR) fft_paired<LOGN, CB, true>(buf, tw);
+        else fft_single<LOGN, CB, true>(buf, tw);
+    }
+};
+template <int LOGN> using RowFft = Fft<LOGN, 1, (LOGN >= 10)>;
+// (a block of one column pairs from 16 KB of it on)
+template <int LOGN, int CB>
+using ColFft = Fft<LOGN, CB, (CB << LOGN) >= 1024 && (CB > 1 || sizeof(cpx) << LOGN >= 16384)>;
 
 // Global loads each thread of a column pass issues before it waits for the first: with a few
 // blocks of LDS-resident columns per compute unit, one load at a time leaves the latency of

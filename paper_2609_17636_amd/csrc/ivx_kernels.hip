@@ -43,6 +43,7 @@ __global__ __launch_bounds__(NT) void k_image_rows(Geom g, const real *__restric
                                                    const real *__restrict__ dq,
                                                    const cpx *__restrict__ tw, cpx *__restrict__ R) {
     constexpr int N = 1 << LOGN;
+    using F = Fft<LOGN, 1, (LOGN >= 11)>;
     __shared__ cpx buf[N + 1]; // + a sink cell for the stores of positions past the end
     __shared__ cpx tws[tw_len<LOGN>()];
     TwStage<LOGN> twr;
@@ -96,16 +97,16 @@ __global__ __launch_bounds__(NT) void k_image_rows(Geom g, const real *__restric
             const int b = b0 + u * NT;
             const real f0 = q0 * dv[u] * a_0[u] * t0[u].combine(p0[u][0], p0[u][1], p0[u][2], p0[u][3]);
             const real f1 = q1 * dv[u] * a_1[u] * t1[u].combine(p1[u][0], p1[u][1], p1[u][2], p1[u][3]);
-            buf[b < nk ? fft_swz((b - nk / 2) & (N - 1)) : N] = cpx{f0, f1};
+            buf[b < nk ? F::at((b - nk / 2) & (N - 1)) : N] = cpx{f0, f1};
         }
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, 1, false>(buf, tws);
+    F::forward(buf, tws);
     cpx *R0 = R + (int64_t)item * g.r_stride + (int64_t)a0 * g.rw;
     cpx *R1 = R0 + g.rw;
     for (int kk = tid; kk <= N / 2; kk += NT) {
-        const cpx z = buf[fft_swz(kk)], zm = buf[fft_swz((N - kk) & (N - 1))];
+        const cpx z = buf[F::at(kk)], zm = buf[F::at((N - kk) & (N - 1))];
         // X = (Z + conj Zm)/2 (row a0), Y = (Z - conj Zm)/(2i) (row a0+1)
         R0[kk] = cpx{real(0.5) * (z.re + zm.re), real(0.5) * (z.im - zm.im)};
         R1[kk] = cpx{real(0.5) * (z.im + zm.im), real(0.5) * (zm.re - z.re)};
@@ -117,8 +118,9 @@ template <int LOGN, int CB>
 __global__ __launch_bounds__(NT) void k_col_fwd(Geom g, const cpx *__restrict__ R,
                                                 const cpx *__restrict__ tw, cpx *__restrict__ ext) {
     constexpr int N = 1 << LOGN;
+    using F = ColFft<LOGN, CB>;
     constexpr int MAXE = 8 * CB;
-    __shared__ cpx buf[fft_len<LOGN, CB>() + 1]; // + a sink cell for the stores of positions past the end
+    __shared__ cpx buf[F::LEN + 1]; // + a sink cell for the stores of positions past the end
     __shared__ cpx tws[tw_len<LOGN>()];
     TwStage<LOGN> twr;
     twr.fetch(tw);
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(NT) void k_col_fwd(Geom g, const cpx *__restrict__ 
     int item, c0;
     if (!col_block<CB>(g, item, c0)) return;
     const int nk = g.nk;
-    for (int i = tid; i < fft_len<LOGN, CB>(); i += NT) buf[i] = cpx{0, 0};
+    for (int i = tid; i < F::LEN; i += NT) buf[i] = cpx{0, 0};
     if (tid == 0) {
         // extended columns fed by this block's source columns: direct copies at
         // src + O + m N, Hermitian mirrors (conjugate, row-reversed) at N - src + O + m N
@@ -168,12 +170,12 @@ __global__ __launch_bounds__(NT) void k_col_fwd(Geom g, const cpx *__restrict__ 
         for (int u = 0; u < COL_LOADS; ++u) {
             const int e = e0 + u * NT, a = e / CB, cc = e - (e / CB) * CB;
             const bool ok = e < nk * CB && c0 + cc < g.rw;
-            buf[ok ? fft_at<LOGN, CB>((a - nk / 2) & (N - 1), cc) : fft_len<LOGN, CB>()] = v[u];
+            buf[ok ? F::at((a - nk / 2) & (N - 1), cc) : F::LEN] = v[u];
         }
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, CB, false>(buf, tws);
+    F::forward(buf, tws);
     cpx *E = ext + (int64_t)item * g.ext_stride;
     const int ne = n_ent;
     for (int e = tid; e < ne * g.eh; e += NT) {
@@ -183,10 +185,10 @@ __global__ __launch_bounds__(NT) void k_col_fwd(Geom g, const cpx *__restrict__ 
         const int t1 = (er - g.O) & (N - 1);
         cpx v;
         if (src & 0x10000) {
-            v = buf[fft_at<LOGN, CB>((N - t1) & (N - 1), cc)];
+            v = buf[F::at((N - t1) & (N - 1), cc)];
             v.im = -v.im;
         } else {
-            v = buf[fft_at<LOGN, CB>(t1, cc)];
+            v = buf[F::at(t1, cc)];
         }
         E[(int64_t)ent_col[en] * g.eh + er] = v; // column-major
     }
@@ -1220,7 +1222,8 @@ template <int LOGN, int CB>
 __global__ __launch_bounds__(NT) void k_col_inv(Geom g, const cpx *__restrict__ E,
                                                 const cpx *__restrict__ tw, cpx *__restrict__ R) {
     constexpr int N = 1 << LOGN;
-    __shared__ cpx buf[fft_len<LOGN, CB>()];
+    using F = ColFft<LOGN, CB>;
+    __shared__ cpx buf[F::LEN];
     __shared__ cpx tws[tw_len<LOGN>()];
     TwStage<LOGN> twr;
     twr.fetch(tw);
@@ -1252,7 +1255,7 @@ __global__ __launch_bounds__(NT) void k_col_inv(Geom g, const cpx *__restrict__ 
                     const cpx m = pair_sum(g, (N - t1) & (N - 1), (N - t2) & (N - 1), m0[u], m1[u]);
                     v = cpx{real(0.5) * (h.re + m.re), real(0.5) * (h.im - m.im)};
                 }
-                buf[fft_at<LOGN, CB>(t1, cc)] = v;
+                buf[F::at(t1, cc)] = v;
             }
         }
     } else {
@@ -1265,17 +1268,17 @@ __global__ __launch_bounds__(NT) void k_col_inv(Geom g, const cpx *__restrict__ 
                 const cpx m = alias_sum(g, Ei, (N - t1) & (N - 1), (N - t2) & (N - 1));
                 v = cpx{real(0.5) * (h.re + m.re), real(0.5) * (h.im - m.im)};
             }
-            buf[fft_at<LOGN, CB>(t1, cc)] = v;
+            buf[F::at(t1, cc)] = v;
         }
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, CB, true>(buf, tws);
+    F::inverse(buf, tws);
     cpx *Ri = R + (int64_t)item * g.r_stride;
     const int nk = g.nk;
     for (int e = tid; e < nk * CB; e += NT) {
         const int a = e / CB, cc = e - (e / CB) * CB;
-        if (c0 + cc < g.rw) Ri[(int64_t)a * g.rw + c0 + cc] = buf[fft_at<LOGN, CB>((a - nk / 2) & (N - 1), cc)];
+        if (c0 + cc < g.rw) Ri[(int64_t)a * g.rw + c0 + cc] = buf[F::at((a - nk / 2) & (N - 1), cc)];
     }
 }
 
@@ -1361,9 +1364,10 @@ __global__ __launch_bounds__(NT) void k_col_inv_slots(Geom g, const int32_t *__r
                                                       const cpx *__restrict__ slots, const cpx *__restrict__ tw,
                                                       cpx *__restrict__ R) {
     constexpr int N = 1 << LOGN;
+    using F = Fft<LOGN, CB, false>;
     // tile rows of the grid: (n_f + O) / T + 1 with T >= 4 and O <= 8
     constexpr int MAXROWS = (N + 8) / 4 + 2;
-    __shared__ cpx buf[fft_len<LOGN, CB>()];
+    __shared__ cpx buf[F::LEN];
     __shared__ cpx tws[tw_len<LOGN>()];
     // slot-list prefix of tile columns vxa - 1 .. vxa + 2 in every tile row: the tiles whose
     // windows reach this block's columns (CB <= T consecutive columns lie in at most two
@@ -1486,17 +1490,17 @@ __global__ __launch_bounds__(NT) void k_col_inv_slots(Geom g, const int32_t *__r
                 const cpx m = alias_from_slots(g, ts, slots, (N - t1) & msk, (N - t2) & msk);
                 v = cpx{real(0.5) * (hr + m.re), real(0.5) * (hi - m.im)};
             }
-            buf[fft_at<LOGN, CB>(t1, cc)] = v;
+            buf[F::at(t1, cc)] = v;
         }
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, CB, true>(buf, tws);
+    F::inverse(buf, tws);
     cpx *Ri = R + (int64_t)item * g.r_stride;
     const int nk = g.nk;
     for (int e = tid; e < nk * CB; e += NT) {
         const int a = e / CB, cc = e - (e / CB) * CB;
-        if (c0 + cc < g.rw) Ri[(int64_t)a * g.rw + c0 + cc] = buf[fft_at<LOGN, CB>((a - nk / 2) & (N - 1), cc)];
+        if (c0 + cc < g.rw) Ri[(int64_t)a * g.rw + c0 + cc] = buf[F::at((a - nk / 2) & (N - 1), cc)];
     }
 }
 
@@ -1508,6 +1512,7 @@ __global__ __launch_bounds__(NT) void k_row_inv(Geom g, const cpx *__restrict__ 
                                                 const real *__restrict__ dq,
                                                 const cpx *__restrict__ tw, real *__restrict__ gp) {
     constexpr int N = 1 << LOGN;
+    using F = RowFft<LOGN>;
     __shared__ cpx buf[N];
     __shared__ cpx tws[tw_len<LOGN>()];
     TwStage<LOGN> twr;
@@ -1541,18 +1546,18 @@ __global__ __launch_bounds__(NT) void k_row_inv(Geom g, const cpx *__restrict__ 
                 x.im = -x.im;
                 y.im = -y.im;
             }
-            buf[fft_swz(kk)] = cpx{x.re - y.im, x.im + y.re}; // x + i y
+            buf[F::at(kk)] = cpx{x.re - y.im, x.im + y.re}; // x + i y
         }
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, 1, true>(buf, tws);
+    F::inverse(buf, tws);
     const real *A = beams + (int64_t)k * nk * nk;
     real *out = gp + (int64_t)item * nk * nk;
     const real s = fscale[c];
     const real q0 = s * dq[a0], q1 = s * dq[a0 + 1];
     for (int b = tid; b < nk; b += NT) {
-        const cpx z = buf[fft_swz((b - nk / 2) & (N - 1))];
+        const cpx z = buf[F::at((b - nk / 2) & (N - 1))];
         const int64_t e0 = (int64_t)a0 * nk + b;
         out[e0] = q0 * dq[b] * A[e0] * z.re;
         out[e0 + nk] = q1 * dq[b] * A[e0 + nk] * z.im;
@@ -1910,18 +1915,19 @@ template <int LOGN>
 __global__ __launch_bounds__(NT) void k_feather_rows(const real *__restrict__ interf, const real *__restrict__ sd,
                                                      cpx *__restrict__ work) {
     constexpr int N = 1 << LOGN, RW = N / 2 + 1;
+    using F = RowFft<LOGN>;
     __shared__ cpx buf[N];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int c = blockIdx.y, a0 = 2 * blockIdx.x;
     const int64_t base = ((int64_t)c * N + a0) * N;
     for (int b = threadIdx.x; b < N; b += NT)
-        buf[fft_swz(b)] = cpx{sd[base + b] - interf[base + b], sd[base + N + b] - interf[base + N + b]};
+        buf[F::at(b)] = cpx{sd[base + b] - interf[base + b], sd[base + N + b] - interf[base + N + b]};
     tw_fill<LOGN>(tws);
     __syncthreads();
-    fft_lds<LOGN, 1, false>(buf, tws);
+    F::forward(buf, tws);
     cpx *W0 = work + ((int64_t)c * N + a0) * RW, *W1 = W0 + RW;
     for (int kk = threadIdx.x; kk < RW; kk += NT) {
-        const cpx z = buf[fft_swz(kk)], zm = buf[fft_swz((N - kk) & (N - 1))];
+        const cpx z = buf[F::at(kk)], zm = buf[F::at((N - kk) & (N - 1))];
         W0[kk] = cpx{real(0.5) * (z.re + zm.re), real(0.5) * (z.im - zm.im)};
         W1[kk] = cpx{real(0.5) * (z.im + zm.im), real(0.5) * (zm.re - z.re)};
     }
@@ -1930,7 +1936,8 @@ __global__ __launch_bounds__(NT) void k_feather_rows(const real *__restrict__ in
 template <int LOGN, int CB>
 __global__ __launch_bounds__(NT) void k_feather_cols(cpx *__restrict__ work, double knorm2) {
     constexpr int N = 1 << LOGN, RW = N / 2 + 1;
-    __shared__ cpx buf[fft_len<LOGN, CB>()];
+    using F = ColFft<LOGN, CB>;
+    __shared__ cpx buf[F::LEN];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int c = blockIdx.y, c0 = blockIdx.x * CB;
     cpx *Wc = work + (int64_t)c * N * RW;
@@ -1945,25 +1952,25 @@ __global__ __launch_bounds__(NT) void k_feather_cols(cpx *__restrict__ work, dou
 #pragma unroll
         for (int u = 0; u < COL_LOADS; ++u) {
             const int e = e0 + u * NT, q = e / CB, cc = e - q * CB;
-            if (e < N * CB) buf[fft_at<LOGN, CB>(q, cc)] = c0 + cc < RW ? v[u] : cpx{0, 0};
+            if (e < N * CB) buf[F::at(q, cc)] = c0 + cc < RW ? v[u] : cpx{0, 0};
         }
     }
     tw_fill<LOGN>(tws);
     __syncthreads();
-    fft_lds<LOGN, CB, false>(buf, tws);
+    F::forward(buf, tws);
     // B(k) with k^2 = (p^2 + q^2) / (n delta)^2; knorm2 = 2 pi^2 sigma^2 / (n delta)^2
     for (int e = threadIdx.x; e < N * CB; e += NT) {
         const int q = e / CB, cc = e - q * CB;
         const int qs = q < N / 2 ? q : q - N, ps = c0 + cc;
         const real bk = (real)exp(-knorm2 * ((double)ps * ps + (double)qs * qs));
-        cpx &z = buf[fft_at<LOGN, CB>(q, cc)];
+        cpx &z = buf[F::at(q, cc)];
         z = cpx{bk * z.re, bk * z.im};
     }
     __syncthreads();
-    fft_lds<LOGN, CB, true>(buf, tws);
+    F::inverse(buf, tws);
     for (int e = threadIdx.x; e < N * CB; e += NT) {
         const int q = e / CB, cc = e - q * CB;
-        if (c0 + cc < RW) Wc[(int64_t)q * RW + c0 + cc] = buf[fft_at<LOGN, CB>(q, cc)];
+        if (c0 + cc < RW) Wc[(int64_t)q * RW + c0 + cc] = buf[F::at(q, cc)];
     }
 }
 
@@ -1971,6 +1978,7 @@ template <int LOGN>
 __global__ __launch_bounds__(NT) void k_feather_rows_inv(const real *__restrict__ interf, const cpx *__restrict__ work,
                                                          real *__restrict__ out) {
     constexpr int N = 1 << LOGN, RW = N / 2 + 1;
+    using F = RowFft<LOGN>;
     __shared__ cpx buf[N];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int c = blockIdx.y, a0 = 2 * blockIdx.x;
@@ -1982,16 +1990,16 @@ __global__ __launch_bounds__(NT) void k_feather_rows_inv(const real *__restrict_
             x.im = -x.im;
             y.im = -y.im;
         }
-        buf[fft_swz(kk)] = cpx{x.re - y.im, x.im + y.re}; // x + i y
+        buf[F::at(kk)] = cpx{x.re - y.im, x.im + y.re}; // x + i y
     }
     tw_fill<LOGN>(tws);
     __syncthreads();
-    fft_lds<LOGN, 1, true>(buf, tws);
+    F::inverse(buf, tws);
     const real sc = real(1) / ((real)N * (real)N);
     const int64_t base = ((int64_t)c * N + a0) * N;
     for (int b = threadIdx.x; b < N; b += NT) {
-        out[base + b] = interf[base + b] + sc * buf[fft_swz(b)].re;
-        out[base + N + b] = interf[base + N + b] + sc * buf[fft_swz(b)].im;
+        out[base + b] = interf[base + b] + sc * buf[F::at(b)].re;
+        out[base + N + b] = interf[base + N + b] + sc * buf[F::at(b)].im;
     }
 }
 

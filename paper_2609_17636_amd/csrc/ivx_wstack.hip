@@ -206,6 +206,7 @@ __global__ __launch_bounds__(NT) void k_wimage_rows(Geom g, WGeom wg, int plane,
                                                     const real *__restrict__ fscale, const real *__restrict__ dq,
                                                     const cpx *__restrict__ tw, cpx *__restrict__ R) {
     constexpr int N = 1 << LOGN;
+    using F = RowFft<LOGN>;
     __shared__ cpx buf[N];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int item = blockIdx.y;
@@ -227,20 +228,21 @@ __global__ __launch_bounds__(NT) void k_wimage_rows(Geom g, WGeom wg, int plane,
         const int64_t e = (int64_t)a * nk + b;
         const real f = qa * dq[b] * A[e] * wg.corr[e] * bilinear(x, g.N, G[2 * e], G[2 * e + 1]);
         const cpx s = unit_phase(w0 * wg.xp[e] + pl * wg.tp[e]);
-        buf[fft_swz((b - nk / 2) & (N - 1))] = cpx{f * s.re, f * s.im};
+        buf[F::at((b - nk / 2) & (N - 1))] = cpx{f * s.re, f * s.im};
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, 1, false>(buf, tws);
+    F::forward(buf, tws);
     cpx *Ra = R + (int64_t)item * wg.r_stride + (int64_t)a * g.ew;
-    for (int ec = tid; ec < g.ew; ec += NT) Ra[ec] = buf[fft_swz((ec - g.O) & (N - 1))];
+    for (int ec = tid; ec < g.ew; ec += NT) Ra[ec] = buf[F::at((ec - g.O) & (N - 1))];
 }
 
 template <int LOGN, int CB>
 __global__ __launch_bounds__(NT) void k_wcol_fwd(Geom g, WGeom wg, int plane, const cpx *__restrict__ R,
                                                  const cpx *__restrict__ tw, cpx *__restrict__ ext) {
     constexpr int N = 1 << LOGN;
-    __shared__ cpx buf[fft_len<LOGN, CB>()];
+    using F = ColFft<LOGN, CB>;
+    __shared__ cpx buf[F::LEN];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int item = blockIdx.y;
     if (plane >= wg.np[item]) return;
@@ -249,20 +251,20 @@ __global__ __launch_bounds__(NT) void k_wcol_fwd(Geom g, WGeom wg, int plane, co
     const int tid = threadIdx.x;
     const int c0 = blockIdx.x * CB;
     const int nk = g.nk;
-    for (int i = tid; i < fft_len<LOGN, CB>(); i += NT) buf[i] = cpx{0, 0};
+    for (int i = tid; i < F::LEN; i += NT) buf[i] = cpx{0, 0};
     __syncthreads();
     const cpx *Ri = R + (int64_t)item * wg.r_stride;
     for (int e = tid; e < nk * CB; e += NT) {
         const int a = e / CB, cc = e - (e / CB) * CB;
-        if (c0 + cc < g.ew) buf[fft_at<LOGN, CB>((a - nk / 2) & (N - 1), cc)] = Ri[(int64_t)a * g.ew + c0 + cc];
+        if (c0 + cc < g.ew) buf[F::at((a - nk / 2) & (N - 1), cc)] = Ri[(int64_t)a * g.ew + c0 + cc];
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, CB, false>(buf, tws);
+    F::forward(buf, tws);
     cpx *E = ext + (int64_t)item * g.ext_stride;
     for (int e = tid; e < CB * g.eh; e += NT) {
         const int cc = e / g.eh, er = e - (e / g.eh) * g.eh;
-        if (c0 + cc < g.ew) E[(int64_t)(c0 + cc) * g.eh + er] = buf[fft_at<LOGN, CB>((er - g.O) & (N - 1), cc)];
+        if (c0 + cc < g.ew) E[(int64_t)(c0 + cc) * g.eh + er] = buf[F::at((er - g.O) & (N - 1), cc)];
     }
 }
 
@@ -273,7 +275,8 @@ template <int LOGN, int CB>
 __global__ __launch_bounds__(NT) void k_wcol_inv(Geom g, WGeom wg, int plane, const cpx *__restrict__ ext,
                                                  const cpx *__restrict__ tw, cpx *__restrict__ R) {
     constexpr int N = 1 << LOGN;
-    __shared__ cpx buf[fft_len<LOGN, CB>()];
+    using F = ColFft<LOGN, CB>;
+    __shared__ cpx buf[F::LEN];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int item = blockIdx.y;
     if (plane >= wg.np[item]) return;
@@ -294,15 +297,15 @@ __global__ __launch_bounds__(NT) void k_wcol_inv(Geom g, WGeom wg, int plane, co
                     si += h.im;
                 }
         }
-        buf[fft_at<LOGN, CB>(t, cc)] = cpx{sr, si};
+        buf[F::at(t, cc)] = cpx{sr, si};
     }
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, CB, true>(buf, tws);
+    F::inverse(buf, tws);
     cpx *Ri = R + (int64_t)item * wg.r_stride;
     for (int e = tid; e < nk * CB; e += NT) {
         const int a = e / CB, cc = e - (e / CB) * CB;
-        if (c0 + cc < wg.ncol) Ri[(int64_t)a * g.ew + c0 + cc] = buf[fft_at<LOGN, CB>((a - nk / 2) & (N - 1), cc)];
+        if (c0 + cc < wg.ncol) Ri[(int64_t)a * g.ew + c0 + cc] = buf[F::at((a - nk / 2) & (N - 1), cc)];
     }
 }
 
@@ -312,6 +315,7 @@ __global__ __launch_bounds__(NT) void k_wrow_inv(Geom g, WGeom wg, int plane, co
                                                  const real *__restrict__ dq, const cpx *__restrict__ tw,
                                                  real *__restrict__ gp) {
     constexpr int N = 1 << LOGN;
+    using F = RowFft<LOGN>;
     __shared__ cpx buf[N];
     __shared__ cpx tws[tw_len<LOGN>()];
     const int item = blockIdx.y;
@@ -330,16 +334,16 @@ __global__ __launch_bounds__(NT) void k_wrow_inv(Geom g, WGeom wg, int plane, co
     for (int i = tid; i < N; i += NT) buf[i] = cpx{0, 0};
     __syncthreads();
     const cpx *Ra = R + (int64_t)item * wg.r_stride + (int64_t)a * g.ew;
-    for (int ec = tid; ec < wg.ncol; ec += NT) buf[fft_swz((ec - g.O) & (N - 1))] = Ra[ec];
+    for (int ec = tid; ec < wg.ncol; ec += NT) buf[F::at((ec - g.O) & (N - 1))] = Ra[ec];
     twr.store(tws);
     __syncthreads();
-    fft_lds<LOGN, 1, true>(buf, tws);
+    F::inverse(buf, tws);
     const real *A = beams + (int64_t)k * nk * nk;
     const real qa = fscale[c] * dq[a];
     const double w0 = wg.w0[item], pl = (double)plane;
     for (int b = tid; b < nk; b += NT) {
         const int64_t e = (int64_t)a * nk + b;
-        const cpx z = buf[fft_swz((b - nk / 2) & (N - 1))];
+        const cpx z = buf[F::at((b - nk / 2) & (N - 1))];
         const cpx s = unit_phase(w0 * wg.xp[e] + pl * wg.tp[e]); // the screen; its conjugate applies
         const real v = (z.re * s.re + z.im * s.im) * wg.corr[e] * qa * dq[b] * A[e];
         out[b] = plane == 0 ? v : out[b] + v;
