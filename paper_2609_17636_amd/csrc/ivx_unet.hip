@@ -129,6 +129,142 @@ __global__ __launch_bounds__(NT) void k_conv3x3(const float *__restrict__ x, int
     }
 }
 
+// LDS-tiled implicit GEMM for the 3x3 convolution: block tile 64 pixels x BN channels
+// (BN = 32 NJ), k chunks of 32 staged in LDS as bf16 (A: [pixel][k], B: [channel][k], rows
+// padded to 40 elements), 4 waves in a 2 x 2 arrangement, each wave 2 x NJ tiles of
+// v_mfma_f32_16x16x32_bf16 (one per chunk).  The next chunk's global loads are issued before
+// the current chunk's matrix products.  (FP32 layers that the kernels below do not take or take slower: conv3x3_layer.)
+constexpr int TBM = 64, TBK = 32, TLD = 40;
+template <int NJ>
+__global__ __launch_bounds__(NT) void k_conv3x3_tiled(const float *__restrict__ x, int n, int h, int w, int cin,
+                                                      const uint16_t *__restrict__ wt, const float *__restrict__ bias,
+                                                      int cout, int relu, const float *__restrict__ mask,
+                                                      int accumulate, float *__restrict__ y) {
+    constexpr int BN = 32 * NJ;
+    __shared__ __align__(16) uint16_t As[TBM * TLD];
+    __shared__ __align__(16) uint16_t Bs[BN * TLD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t P = (int64_t)n * h * w;
+    const int K = 9 * cin;
+    const int64_t m0 = (int64_t)blockIdx.x * TBM;
+    const int n0 = blockIdx.y * BN;
+    // ---- global -> register staging: A (pixel am, k quarter aq), B (channel rows)
+    const int am = tid >> 2, aq = (tid & 3) * 8;
+    const int64_t ap = m0 + am;
+    int apn = 0, apy = 0, apx = 0;
+    const bool apv = ap < P;
+    if (apv) {
+        apn = (int)(ap / ((int64_t)h * w));
+        const int r = (int)(ap - (int64_t)apn * h * w);
+        apy = r / w;
+        apx = r - apy * w;
+    }
+    constexpr int BPIECES = BN * (TBK / 8);           // 8-element pieces of one B chunk
+    constexpr int BROWS = (BPIECES + NT - 1) / NT;    // per thread (1 or 2)
+    uint16_t ra[8];
+    uint16_t rb[BROWS][8];
+    auto gload = [&](int k0) {
+#pragma unroll
+        for (int hlf = 0; hlf < 2; ++hlf) {
+            const int k = k0 + aq + 4 * hlf;
+            float4 v = float4{0.f, 0.f, 0.f, 0.f};
+            if (apv && k < K) {
+                const int tap = k / cin, c = k - tap * cin;
+                const int yy = apy + tap / 3 - 1, xx = apx + tap % 3 - 1;
+                if (yy >= 0 && yy < h && xx >= 0 && xx < w)
+                    v = *reinterpret_cast<const float4 *>(x + (((int64_t)apn * h + yy) * w + xx) * cin + c);
+            }
+            ra[4 * hlf + 0] = f2bf(v.x);
+            ra[4 * hlf + 1] = f2bf(v.y);
+            ra[4 * hlf + 2] = f2bf(v.z);
+            ra[4 * hlf + 3] = f2bf(v.w);
+        }
+#pragma unroll
+        for (int b = 0; b < BROWS; ++b) {
+            const int e = tid + b * NT;
+            const int o = e >> 2, bq = (e & 3) * 8;
+#pragma unroll
+            for (int hlf = 0; hlf < 2; ++hlf) {
+                const int k = k0 + bq + 4 * hlf;
+                uint2 u = uint2{0u, 0u};
+                if (e < BPIECES && n0 + o < cout && k < K) u = *reinterpret_cast<const uint2 *>(wt + (int64_t)(n0 + o) * K + k);
+                rb[b][4 * hlf + 0] = (uint16_t)(u.x & 0xFFFFu);
+                rb[b][4 * hlf + 1] = (uint16_t)(u.x >> 16);
+                rb[b][4 * hlf + 2] = (uint16_t)(u.y & 0xFFFFu);
+                rb[b][4 * hlf + 3] = (uint16_t)(u.y >> 16);
+            }
+        }
+    };
+    auto sstore = [&]() {
+        uint4 va;
+        va.x = ra[0] | ((uint32_t)ra[1] << 16);
+        va.y = ra[2] | ((uint32_t)ra[3] << 16);
+        va.z = ra[4] | ((uint32_t)ra[5] << 16);
+        va.w = ra[6] | ((uint32_t)ra[7] << 16);
+        *reinterpret_cast<uint4 *>(&As[am * TLD + aq]) = va;
+#pragma unroll
+        for (int b = 0; b < BROWS; ++b) {
+            const int e = tid + b * NT;
+            if (e >= BPIECES) continue;
+            const int o = e >> 2, bq = (e & 3) * 8;
+            uint4 vb;
+            vb.x = rb[b][0] | ((uint32_t)rb[b][1] << 16);
+            vb.y = rb[b][2] | ((uint32_t)rb[b][3] << 16);
+            vb.z = rb[b][4] | ((uint32_t)rb[b][5] << 16);
+            vb.w = rb[b][6] | ((uint32_t)rb[b][7] << 16);
+            *reinterpret_cast<uint4 *>(&Bs[o * TLD + bq]) = vb;
+        }
+    };
+    // ---- matrix products: wave (wr, wc) owns rows 32 wr .. +32, columns 16 NJ wc .. +16 NJ
+    const int wr = wave >> 1, wc = wave & 1;
+    const int row = lane & 15, kq = lane >> 4;
+    f32x4 acc[2][NJ];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nch = (K + TBK - 1) / TBK;
+    gload(0);
+    for (int kc = 0; kc < nch; ++kc) {
+        __syncthreads();
+        sstore();
+        __syncthreads();
+        if (kc + 1 < nch) gload((kc + 1) * TBK);
+        static_assert(TBK == 32, "one 16x16x32 product per chunk");
+        bf16x8 af[2], bfr[NJ];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            af[i] = as_bf16x8(*reinterpret_cast<const uint4 *>(&As[(wr * 32 + i * 16 + row) * TLD + 8 * kq]));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            bfr[j] = as_bf16x8(*reinterpret_cast<const uint4 *>(&Bs[(wc * 16 * NJ + j * 16 + row) * TLD + 8 * kq]));
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] = mma(af[i], bfr[j], acc[i][j]);
+    }
+    // ---- epilogue: D row (pixel) 4 kq + v, column (channel) = row index of the lane
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int co = n0 + wc * 16 * NJ + j * 16 + row;
+            if (co >= cout) continue;
+            const float bb = bias ? bias[co] : 0.f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t pp = m0 + wr * 32 + i * 16 + 4 * kq + v;
+                if (pp >= P) continue;
+                const int64_t o = pp * cout + co;
+                float val = acc[i][j][v] + bb;
+                if (relu) val = fmaxf(val, 0.f);
+                if (mask && !(mask[o] > 0.f)) val = 0.f;
+                if (accumulate) val += y[o];
+                y[o] = val;
+            }
+        }
+}
+
 // ------------------------------------------------- 3x3 convolution, one wave per output tile
 // Input of a convolution as 8-channel pieces: bf16 activations (16 bytes a piece) or FP32 ones
 // rounded to bf16 as they are loaded.  A second source continues the channels of the first, and the
@@ -226,8 +362,7 @@ __device__ __forceinline__ void store_out(const ConvOut &out, f32x4 acc, int64_t
     }
 }
 
-// Channel counts that the patch kernel below does not take (not both multiples of 32, or more inputs
-// than its patch holds).  Output tile of one wave: 16 MI pixels x 16 NJ channels, K in 32-wide steps, operands
+// Channel counts that the patch kernel below does not take (not both multiples of 32).  Output tile of one wave: 16 MI pixels x 16 NJ channels, K in 32-wide steps, operands
 // straight from global memory (each lane's 8 consecutive k are 16 contiguous bytes of a pixel or of a weight
 // row), DEPTH steps in flight; bound by those loads.
 // The order of the steps fixes the bits of the sums: tap-major, or (chunks) channel-chunk-major.
@@ -352,7 +487,7 @@ k_conv3x3_wave(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__res
 
 // A block of WM x WN waves owns 2 WM rows x 32 columns of one image and 16 NJ WN output channels.  The
 // patch with its one-pixel halo is staged in LDS once, all input channels of it (the order of the steps
-// runs over channels inside the taps), and serves the nine taps; the weights stay in the vector cache,
+// runs over channels inside the taps) or, where these do not fit, cp at a time, and serves the nine taps; the weights stay in the vector cache,
 // DEPTH steps ahead (9 cin / 32 steps: DEPTH divides them).  A wave takes 64 pixels x 16 NJ channels: per 32-wide
 // step 4 LDS reads, NJ weight loads, 4 NJ products.  Position rows are padded by 16 bytes, so that eight
 // lanes' reads of consecutive positions cover all banks.
@@ -361,10 +496,10 @@ k_conv3x3_wave(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__res
 // chunk and tap from FP32 activations these took 155 and 133 us.  One 256^2 image, whose deep levels
 // are chains of 36 to 108 dependent steps on few blocks: 10 to 20 us a layer, from 47 to 110.
 constexpr int PT_W = 32, PT_PW = PT_W + 2;
-template <typename T, int WM, int WN, int NJ, int DEPTH>
+template <typename T, int WM, int WN, int NJ, int DEPTH, bool PARTS>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 8))) void
-k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__restrict__ wt, int packed, int cout, int chunks,
-                ConvOut out) {
+k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, int cp, const uint16_t *__restrict__ wt, int packed, int cout,
+                int chunks, ConvOut out) {
     extern __shared__ __align__(16) uint16_t Ps[];
     constexpr int NTH = 64 * WM * WN, POS = (2 * WM + 2) * PT_PW, U = 8;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -373,16 +508,16 @@ k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__re
     const int t = blockIdx.x, img = t / (tx * ty), r = t - img * tx * ty;
     const int y0 = (r / tx) * (2 * WM), x0 = (r % tx) * PT_W;
     const int n0 = (blockIdx.y * WN + wn) * (16 * NJ);
-    const int K = 9 * cin, ca = in.ca, cb = cin - in.ca, ld = cin + 8;
-    {
+    const int K = 9 * cin, ca = in.ca, cb = cin - in.ca, ld = (PARTS ? cp : cin) + 8;
+    auto stage_part = [&](int p0, int p1) { // channels [p0, p1) of the patch
         const int yt = y0 > 0 ? y0 - 1 : 0, sh = in.half0;
         const int64_t base = (int64_t)img * h * w + (int64_t)yt * w;
         const int64_t base0 = sh ? ((int64_t)img * (h >> 1) + (yt >> 1)) * (w >> 1) : base;
         const __amdgpu_buffer_rsrc_t v0 = view(in.x0 + base0 * ca, ((sh ? (int64_t)n * (h >> 1) * (w >> 1) : (int64_t)n * h * w) - base0) * ca * (int)sizeof(T));
         const __amdgpu_buffer_rsrc_t v1 = view(in.x1 + base * cb, ((int64_t)n * h * w - base) * cb * (int)sizeof(T));
-        // the cs channels of one source, from channel `at0` of the patch on
-        auto stage = [&](const __amdgpu_buffer_rsrc_t &v, int cs, int at0, int sh) {
-            const int pieces = cs / 8;
+        // channels [lo, hi) of a source of cs, from channel `at0` of the part on
+        auto stage = [&](const __amdgpu_buffer_rsrc_t &v, int cs, int lo, int hi, int at0, int sh) {
+            const int pieces = (hi - lo) / 8;
             const float inv = 1.f / (float)pieces; // ((e + 1/2) inv is further from an integer than its rounding)
             for (int e0 = tid; e0 < POS * pieces; e0 += U * NTH) {
                 uint4 q[U];
@@ -394,23 +529,21 @@ k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__re
                     const bool ok = e < POS * pieces && yy >= 0 && yy < h && xx >= 0 && xx < w;
                     const unsigned p = (unsigned)(((yy >> sh) - (yt >> sh)) * (w >> sh) + (xx >> sh));
                     at[u] = e < POS * pieces ? pos * ld + at0 + c : POS * ld; // (past the end: a spare piece)
-                    q[u] = load_raw<T>(v, ok ? (p * cs + c) * (unsigned)sizeof(T) : NO_PIECE);
+                    q[u] = load_raw<T>(v, ok ? (p * cs + lo + c) * (unsigned)sizeof(T) : NO_PIECE);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) *reinterpret_cast<uint4 *>(&Ps[at[u]]) = q[u];
             }
         };
-        stage(v0, ca, 0, sh);
-        if (cb) stage(v1, cb, ca, 0);
-    }
+        if (p0 < ca) stage(v0, ca, p0, min(p1, ca), 0, sh);
+        if (p1 > ca) stage(v1, cb, max(p0 - ca, 0), p1 - ca, max(ca - p0, 0), 0);
+    };
     const __amdgpu_buffer_rsrc_t rw = view(wt + (int64_t)n0 * K, (int64_t)16 * NJ * K * 2);
     unsigned wv0[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) wv0[j] = packed ? (unsigned)(16 * j * K + 8 * lane) * 2u : (unsigned)((16 * j + row) * K + 8 * kq) * 2u;
-    // The next step to load: inner and outer position (tap and chunk, or chunk and tap), k in bytes.
-    const int nc = cin / 32, steps = 9 * nc, inner = chunks ? 9 : nc, outer = chunks ? nc : 9;
-    const int dk = chunks ? 2 * cin : 64, back = chunks ? 64 - 16 * cin : 64;
-    int s = 0, so = 0, k2 = 0;
+    // The next step to load: inner and outer position (tap and chunk of the part, or chunk and tap), k in bytes.
+    int s = 0, so = 0, k2 = 0, inner = 0, outer = 0, dk = 0, back = 0;
     u32x4 wv[DEPTH][NJ];
     int off[DEPTH]; // LDS element offset of the step
 #define IVX_STEP_LOAD(d)                                                                                               \
@@ -425,11 +558,6 @@ k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__re
         so += wrap;                                                                                                    \
         k2 += wrap ? back : dk;                                                                                        \
     } while (0)
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-        IVX_STEP_LOAD(d);
-        __builtin_amdgcn_sched_barrier(0); // (in this order: the loop's waits count them)
-    }
     f32x4 acc[NJ][4];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -439,27 +567,45 @@ k_conv3x3_patch(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__re
     auto pixels = [&](int i, int at) {
         return as_bf16x8(*reinterpret_cast<const uint4 *>(a0 + at + ((i >> 1) * PT_PW + 16 * (i & 1)) * ld));
     };
-    __syncthreads();
-    bf16x8 a[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = pixels(i, 0);
-    for (int s0 = 0; s0 < steps; s0 += DEPTH) { // (9 nc steps: a multiple of DEPTH)
+    int p0 = 0;
+    do { // (once unless PARTS)
+        const int nc = (PARTS ? min(cp, cin - p0) : cin) / 32, steps = 9 * nc;
+        inner = chunks ? 9 : nc;
+        outer = chunks ? nc : 9;
+        dk = chunks ? 2 * cin : 64;
+        back = chunks ? 64 - 16 * cin : 2 * cin - 64 * (nc - 1);
+        s = so = 0;
+        k2 = 2 * p0;
+        if (PARTS && p0 > 0) __syncthreads(); // the last part's operands are read
+        stage_part(p0, p0 + 32 * nc);
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
-            const int next = off[(d + 1) % DEPTH]; // (the slot of step s0 + DEPTH holds it by now)
-            bf16x8 an[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) an[i] = pixels(i, next);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][i] = mma(__builtin_bit_cast(bf16x8, wv[d][j]), a[i], acc[j][i]);
-            __builtin_amdgcn_sched_barrier(0); // (the loads of a step stay DEPTH steps ahead of their use)
             IVX_STEP_LOAD(d);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = an[i];
+            __builtin_amdgcn_sched_barrier(0); // (in this order: the loop's waits count them)
         }
-    }
+        __syncthreads();
+        bf16x8 a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = pixels(i, 0);
+        for (int s0 = 0; s0 < steps; s0 += DEPTH) { // (9 nc steps: a multiple of DEPTH)
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                const int next = off[(d + 1) % DEPTH]; // (the slot of step s0 + DEPTH holds it by now)
+                bf16x8 an[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) an[i] = pixels(i, next);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[j][i] = mma(__builtin_bit_cast(bf16x8, wv[d][j]), a[i], acc[j][i]);
+                __builtin_amdgcn_sched_barrier(0); // (the loads of a step stay DEPTH steps ahead of their use)
+                IVX_STEP_LOAD(d);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[i] = an[i];
+            }
+        }
+        p0 += cp;
+    } while (PARTS && p0 < cin);
 #undef IVX_STEP_LOAD
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1140,19 +1286,33 @@ unsigned nblocks(int64_t n) { return (unsigned)((n + NT - 1) / NT); }
 bool rows_fit(int rows, int w, int c, size_t size) { return (int64_t)rows * (w + 64) * c * (int64_t)size < (int64_t)1 << 31; }
 
 constexpr size_t LDS_MAX = 160 * 1024;
-size_t patch_lds(int wm, int cin) { return ((size_t)(2 * wm + 2) * PT_PW * (cin + 8) + 8) * sizeof(uint16_t); }
+size_t patch_lds(int wm, int cp) { return ((size_t)(2 * wm + 2) * PT_PW * (cp + 8) + 8) * sizeof(uint16_t); }
+
+// Channels of a patch that are staged together: all while they fit (in a launch of more than two blocks a CU, blocks
+// of two waves: 64 KB, so that two of them still share a CU), else equal parts of at most 80 KB (two waves: 53).
+// 768 -> 256 channels at 4 x 64^2 from FP32 activations: 123 us, 131 in parts of 53 KB, 472 from global memory;
+// 640 -> 96 at 4 x 64^2: 53 (80 in parts of 80 KB); 288 -> 96 at 4 x 128^2: 79, 119 with the small tile;
+// at 1 x 128^2 (768 blocks) 26, 38 unparted, and at 1 x 32^2 18 : 16.
+int patch_channels(int waves, int wm, int cin, int64_t blocks) {
+    if (patch_lds(wm, cin) <= (waves > 2 || blocks <= 512 ? LDS_MAX : 64 * 1024)) return cin;
+    const int chunks = cin / 32;
+    int parts = 2;
+    while (patch_lds(wm, (chunks + parts - 1) / parts * 32) > (waves > 2 ? 80 * 1024 : 53 * 1024)) ++parts;
+    return (chunks + parts - 1) / parts * 32;
+}
 
 template <typename T, int WM, int WN, int NJ, int DEPTH>
 hipError_t conv3x3_patch(const ConvIn<T> &in, int n, int h, int w, int cin, const uint16_t *wt, int packed, int cout, int chunks,
                          const ConvOut &out, hipStream_t st) {
-    const size_t lds = patch_lds(WM, cin);
+    const int64_t tiles = (int64_t)n * ((h + 2 * WM - 1) / (2 * WM)) * ((w + PT_W - 1) / PT_W);
+    const int cp = patch_channels(WM * WN, WM, cin, tiles * (cout / (16 * NJ * WN)));
+    const size_t lds = patch_lds(WM, cp);
+    const auto kernel = cp < cin ? k_conv3x3_patch<T, WM, WN, NJ, DEPTH, true> : k_conv3x3_patch<T, WM, WN, NJ, DEPTH, false>;
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)k_conv3x3_patch<T, WM, WN, NJ, DEPTH>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+        const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
         if (e != hipSuccess) return e;
     }
-    const int64_t tiles = (int64_t)n * ((h + 2 * WM - 1) / (2 * WM)) * ((w + PT_W - 1) / PT_W);
-    k_conv3x3_patch<T, WM, WN, NJ, DEPTH><<<dim3((unsigned)tiles, cout / (16 * NJ * WN)), 64 * WM * WN, lds, st>>>(in, n, h, w, cin, wt, packed, cout, chunks, out);
+    kernel<<<dim3((unsigned)tiles, cout / (16 * NJ * WN)), 64 * WM * WN, lds, st>>>(in, n, h, w, cin, cp, wt, packed, cout, chunks, out);
     return hipGetLastError();
 }
 
@@ -1166,7 +1326,8 @@ void conv3x3_wave(const ConvIn<T> &in, int n, int h, int w, int cin, const uint1
 }
 
 // cin % 8 == 0, cout % 16 == 0.  The output tile of a wave: the largest whose launch still has two
-// waves per SIMD (each halving of the tile doubles the operand loads per product), at smaller problems
+// waves per SIMD (one for 32 x 32, 56 -> 64 at 128^2 17.6 : 13.4 us, and for 64 x 16 where no step spans taps, 64 -> 16
+// at 256^2 33 : 24, but 40 -> 16 17 : 19; each halving of the tile doubles the operand loads per product), at smaller problems
 // single 16 x 16 tiles with eight steps in flight.
 template <typename T>
 hipError_t conv3x3(const ConvIn<T> &in, int n, int h, int w, int cin, const uint16_t *wt, int packed, int cout,
@@ -1182,7 +1343,7 @@ hipError_t conv3x3(const ConvIn<T> &in, int n, int h, int w, int cin, const uint
         // blocks: one 32^2 image of 256 channels in 14 us, 29 with the large tile's three steps)
         const bool big = waves(4, cout % 64 == 0 ? 4 : 2) >= 1024;
 #define IVX_PATCH(WM, WN, NJ, DEPTH)                                                                                    \
-    if (patch_lds(WM, cin) <= LDS_MAX && rows_fit(2 * WM + 2, w, cin, sizeof(T)))                                       \
+    if (rows_fit(2 * WM + 2, w, cin, sizeof(T)))                                                                        \
     return conv3x3_patch<T, WM, WN, NJ, DEPTH>(in, n, h, w, cin, wt, packed, cout, chunks, out, st)
         if (big && cout % 128 == 0) IVX_PATCH(2, 2, 4, 3);
         if (big && cout % 64 == 0) IVX_PATCH(4, 1, 4, 3);
@@ -1194,20 +1355,47 @@ hipError_t conv3x3(const ConvIn<T> &in, int n, int h, int w, int cin, const uint
     constexpr int64_t FULL = 2048;
     if (cout % 64 == 0 && waves(4, 4) >= FULL) conv3x3_wave<T, 4, 4, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
     else if (cout % 32 == 0 && waves(4, 2) >= FULL) conv3x3_wave<T, 4, 2, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
-    else if (cout % 32 == 0 && waves(2, 2) >= FULL) conv3x3_wave<T, 2, 2, 4>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
-    else if (waves(4, 1) >= FULL) conv3x3_wave<T, 4, 1, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    else if (cout % 32 == 0 && waves(2, 2) >= FULL / 2) conv3x3_wave<T, 2, 2, 4>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
+    else if (waves(4, 1) >= (cin % 32 == 0 ? FULL / 2 : FULL)) conv3x3_wave<T, 4, 1, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
     else conv3x3_wave<T, 1, 1, 8>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
     return hipGetLastError();
 }
 
-// FP32 input of 4, 12, ... channels
-hipError_t conv3x3_narrow(const float *x, int n, int h, int w, int cin, const uint16_t *wt, const float *bias, int cout,
+// FP32 input, any channel count that 4 divides
+hipError_t conv3x3_rows(const float *x, int n, int h, int w, int cin, const uint16_t *wt, const float *bias, int cout,
                           int relu, const float *mask, int accumulate, float *y, uint16_t *yb, hipStream_t st) {
     const unsigned gx = (unsigned)(((int64_t)n * h * w + 63) / 64);
-    if (cout % 64 == 0) k_conv3x3<4><<<dim3(gx, cout / 64), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
+    if (cin >= 16 && cout % 32 == 0 && !yb) {
+        if (cout % 64 == 0) k_conv3x3_tiled<2><<<dim3(gx, cout / 64), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
+        else k_conv3x3_tiled<1><<<dim3(gx, cout / 32), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y);
+    } else if (cout % 64 == 0) k_conv3x3<4><<<dim3(gx, cout / 64), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
     else if (cout % 32 == 0) k_conv3x3<2><<<dim3(gx, cout / 32), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
     else k_conv3x3<1><<<dim3(gx, (cout + 15) / 16), NT, 0, st>>>(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, yb);
     return hipGetLastError();
+}
+
+// A layer on FP32 activations with weights in rows.  The wave kernel reads every tap of a pixel again, from L2
+// while the pixels in flight fit there; the kernels above stage them in LDS or take few channels.  Where cin is no
+// multiple of 32 these are the faster ones (us, wave kernel : they) at
+//   32 or 64 output channels of at most 24: 16 -> 32 at 3 x 128^2 15.3 : 9.3, at 4 x 256^2 33 : 27, 24 -> 64 49 : 42
+//   32 of more: 48 -> 32 at 3 x 128^2 27 : 18, at 4 x 256^2 90 : 64 (below 32,768 pixels 10.5 : 13.5; 248 -> 32 at 4 x 128^2 88 : 104)
+//   multiples of 64 of more, 40,000 to 131,071 pixels: 208 -> 64 at 1 x 256^2 113 : 90 (2 x 256^2 156 : 183)
+//   other counts of more than 16, more than 160,000 pixels, where the input leaves L2: 48 -> 48 at 4 x 256^2 284 : 205
+//   (2 x 256^2 77 : 104), 144 -> 48 813 : 711 (238 : 357), 72 -> 96 492 : 324 (130 : 168)
+hipError_t conv3x3_layer(const float *x, int n, int h, int w, int cin, const uint16_t *wt, const float *bias, int cout,
+                         int relu, const float *mask, int accumulate, float *y, hipStream_t st) {
+    const int64_t P = (int64_t)n * h * w;
+    const bool few = cout % 32 == 0 && cin <= 24 && P >= 16384;
+    const bool many = cout % 64 == 0 ? P >= 40000 && P < 131072 : (cout == 32 && cin < 128 && P >= 32768) || (cin > 16 && P > 160000);
+    if (cin % 8 != 0 || (cin % 32 != 0 && (few || many)) || !rows_fit(4, w, cin, sizeof(float)))
+        return conv3x3_rows(x, n, h, w, cin, wt, bias, cout, relu, mask, accumulate, y, nullptr, st);
+    ConvOut o{};
+    o.y = y;
+    o.bias = bias;
+    o.relu = relu;
+    o.accumulate = accumulate;
+    o.maskf = mask;
+    return conv3x3<float>(ConvIn<float>{x, nullptr, cin, 0}, n, h, w, cin, wt, 0, cout, o, st);
 }
 
 int64_t gw_splits(int n, int h, int w) { return ((int64_t)n * h * w + GW_PIX - 1) / GW_PIX; }
@@ -1438,7 +1626,7 @@ hipError_t forward(ivx_unet *u, const float *x, int B, bool keep, hipStream_t st
         const int h = lvl_h(u, l), w = lvl_w(u, l);
         const ConvLayer &a = u->conv[enc_a(l)], &b = u->conv[enc_b(l)];
         if (l == 0) {
-            e = conv3x3_narrow(u->xin, B, h, w, a.cin, a.wbf, u->params + a.b_off, a.cout, 1, nullptr, 0, nullptr, u->ea[0], st);
+            e = conv3x3_rows(u->xin, B, h, w, a.cin, a.wbf, u->params + a.b_off, a.cout, 1, nullptr, 0, nullptr, u->ea[0], st);
         } else {
             k_pool2_bf16<<<nblocks((int64_t)B * h * w * (u->ch[l - 1] / 8)), NT, 0, st>>>(u->ebb[l - 1], B, 2 * h, 2 * w,
                                                                                           u->ch[l - 1], u->pool[l]);
@@ -1734,17 +1922,7 @@ ivx_status ivx_nn_conv3x3(const float *x, int32_t n, int32_t h, int32_t w, int32
                           void *stream) {
     if (!x || !weight || !y || n < 1 || h < 1 || w < 1 || cin < 4 || cin % 4 || cout < 16 || cout % 16)
         return set_error(IVX_EINVAL, "bad conv3x3 arguments");
-    if (cin % 8 == 0 && rows_fit(4, w, cin, sizeof(float))) {
-        ConvOut o{};
-        o.y = y;
-        o.bias = bias;
-        o.relu = relu;
-        o.accumulate = accumulate;
-        o.maskf = mask;
-        UHIP(conv3x3<float>(ConvIn<float>{x, nullptr, cin, 0}, n, h, w, cin, weight, 0, cout, o, (hipStream_t)stream));
-    } else {
-        UHIP(conv3x3_narrow(x, n, h, w, cin, weight, bias, cout, relu, mask, accumulate, y, nullptr, (hipStream_t)stream));
-    }
+    UHIP(conv3x3_layer(x, n, h, w, cin, weight, bias, cout, relu, mask, accumulate, y, (hipStream_t)stream));
     return IVX_OK;
 }
 

@@ -1,0 +1,78 @@
+"""3x3 convolutions at sizes that take each of their kernels' larger tiles (GPU), against the FP64 layer oracle
+on bands of rows: pixels of a wave that run over row and image boundaries, steps that span taps, channels staged in
+parts, and the FP32 layers that go to the kernels for any channel count.
+
+Operands are exact in bf16 on both sides, so the difference is the FP32 summation error, at most
+K u sum|terms| with K = 9 cin + 2 terms and u = 2^-24.  The network: an activation within FP32 error of a bf16
+rounding boundary may round the other way (2^-8 of that operand), so relative L2 differences of 1e-2
+forward and 2e-2 per parameter block of the gradient.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import unet as U  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+U24 = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def nn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_17636_amd import unet
+
+    return unet
+
+
+def _rows(x, w, b, r0, r1):
+    """Output rows [r0, r1) of the layer."""
+    lo, hi = max(r0 - 1, 0), min(r1 + 1, x.shape[1])
+    return U.conv3x3(x[:, lo:hi], w, b)[:, r0 - lo:r1 - lo]
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (1, 363, 365, 24, 16), (1, 363, 365, 32, 16), (3, 211, 215, 16, 48),     # one wave 64 pixels x 16 channels
+    (1, 363, 365, 40, 64), (1, 363, 365, 40, 96), (1, 129, 127, 40, 96),     # 64 x 64, 64 x 32, 32 x 32
+    (1, 9, 35, 608, 64), (1, 11, 67, 640, 96), (1, 148, 150, 288, 96),       # channels of a patch in parts,
+    (2, 148, 150, 288, 64), (1, 182, 184, 416, 128),                         # small and large tiles
+    (1, 21, 23, 20, 32), (1, 21, 23, 36, 64), (2, 130, 131, 24, 64), (1, 403, 401, 48, 48)])  # any channel count
+def test_conv3x3_variants(nn, n, h, w, cin, cout):
+    g = torch.Generator(device="cuda").manual_seed(cin + cout + h)
+    x, wt, b = (torch.randn(s, generator=g, device="cuda") for s in ((n, h, w, cin), (cout, 3, 3, cin), (cout,)))
+    mask, y0 = (torch.randn((n, h, w, cout), generator=g, device="cuda") for _ in range(2))
+    y = nn.conv3x3(x, nn.to_bf16(wt), bias=b, relu=True, mask=mask, accumulate=True, out=y0.clone()).cpu().numpy()
+    qx, qw, bb = U.bf16(x.cpu().numpy()), U.bf16(wt.cpu().numpy()), b.cpu().numpy().astype(np.float64)
+    on, start = mask.cpu().numpy() > 0, y0.cpu().numpy().astype(np.float64)
+    for r0 in sorted({0, max(0, h // 2 - 2), max(0, h - 4)}):
+        r1 = min(h, r0 + 4)
+        want = np.where(on[:, r0:r1], np.maximum(_rows(qx, qw, bb, r0, r1), 0.0), 0.0) + start[:, r0:r1]
+        size = _rows(np.abs(qx), np.abs(qw), np.abs(bb), r0, r1) + np.abs(start[:, r0:r1])
+        assert np.all(np.abs(y[:, r0:r1] - want) <= (9 * cin + 2) * U24 * size)
+
+
+def test_network_of_narrow_layers(nn):
+    """16 and 48 input channels (steps span taps, two sources, the first at half resolution) on images of more
+    than 131,072 pixels together."""
+    levels, base, batch, h, w = 2, 16, 3, 212, 216
+    net = nn.UNet(levels=levels, base=base, max_batch=batch, height=h, width=w, seed=3)
+    rng = np.random.default_rng(5)
+    p = net.get_params()
+    p += (rng.standard_normal(p.size) * 0.01).astype(p.dtype)
+    net.set_params(p)
+    x, t = rng.random((2, batch, h, w)).astype(np.float32)
+    x4 = np.zeros((batch, h, w, 4))
+    x4[..., 0] = x
+    want, _ = U.unet_forward(x4, U.unpack(p.astype(np.float64), levels, base, 4), levels, round_bf16=True)
+    y = net.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.linalg.norm(y - want) <= 1e-2 * np.linalg.norm(want)
+    _, g = net.loss_grad(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda())
+    _, wg = U.unet_loss_grad(x4, t, p.astype(np.float64), levels, base, 4, round_bf16=True)
+    o = 0
+    for name, shp in U.unet_param_shapes(levels, base, 4):
+        k = int(np.prod(shp)) if shp else 1
+        assert np.linalg.norm(g[o:o + k] - wg[o:o + k]) <= 2e-2 * np.linalg.norm(wg[o:o + k]), name
+        o += k
