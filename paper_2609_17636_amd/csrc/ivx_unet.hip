@@ -951,32 +951,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 8))) void
     }
 }
 
-// out[i] = sum over splits of part[z][i] in a fixed order: block = 64 consecutive i x 16
-// interleaved split groups, combined in LDS (four groups left the 2,048 splits of the input layer to
-// 19 blocks: 132 us).  i < nw goes to dw, the rest to db.
-__global__ __launch_bounds__(1024) void k_sum_splits(const float *__restrict__ part, int splits, int64_t len,
-                                                     int64_t nw, float *__restrict__ dw, float *__restrict__ db) {
-    __shared__ float sh[16][64];
+// out[i] = sum over splits of part[z][i] in a fixed order: block = 64 consecutive i x G
+// interleaved split groups, combined in LDS.  i < nw goes to dw, the rest to db.  Sixteen groups for many
+// splits of few weights (four left the 2,048 splits of the input layer to 19 blocks: 132 us), four for few splits of
+// many, whose blocks twelve idle groups slowed down (four splits of 512 -> 512 channels: the gradient 109 -> 151 us).
+template <int G>
+__global__ __launch_bounds__(64 * G) void k_sum_splits(const float *__restrict__ part, int splits, int64_t len,
+                                                       int64_t nw, float *__restrict__ dw, float *__restrict__ db) {
+    __shared__ float sh[G][64];
     const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + l;
     float s = 0.f;
     if (i < len) {
         int z = g;
-        for (; z + 48 < splits; z += 64) {
+        for (; z + 3 * G < splits; z += 4 * G) {
             float t[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) t[u] = part[(int64_t)(z + 16 * u) * len + i];
+            for (int u = 0; u < 4; ++u) t[u] = part[(int64_t)(z + G * u) * len + i];
 #pragma unroll
             for (int u = 0; u < 4; ++u) s += t[u];
         }
-        for (; z < splits; z += 16) s += part[(int64_t)z * len + i];
+        for (; z < splits; z += G) s += part[(int64_t)z * len + i];
     }
     sh[g][l] = s;
     __syncthreads();
     if (g == 0 && i < len) {
         float t = 0.f;
 #pragma unroll
-        for (int q = 0; q < 16; q += 4) t += (sh[q][l] + sh[q + 1][l]) + (sh[q + 2][l] + sh[q + 3][l]);
+        for (int q = 0; q < G; q += 4) t += (sh[q][l] + sh[q + 1][l]) + (sh[q + 2][l] + sh[q + 3][l]);
         if (i < nw) dw[i] = t;
         else db[i - nw] = t;
     }
@@ -1427,23 +1429,26 @@ int64_t gw_part_len(int n, int h, int w, int cin, int cout) {
 
 void sum_splits(const float *part, int64_t splits, int cin, int cout, float *dw, float *db, hipStream_t st) {
     const int64_t nw = (int64_t)cout * 9 * cin, len = nw + cout;
-    k_sum_splits<<<(unsigned)((len + 63) / 64), 1024, 0, st>>>(part, (int)splits, len, nw, dw, db);
+    const unsigned blocks = (unsigned)((len + 63) / 64);
+    if (splits > 64) k_sum_splits<16><<<blocks, 64 * 16, 0, st>>>(part, (int)splits, len, nw, dw, db);
+    else k_sum_splits<4><<<blocks, 64 * 4, 0, st>>>(part, (int)splits, len, nw, dw, db);
 }
 
 bool gw_patch(int cin, int cout) { return cin % 8 == 0 && cout % 8 == 0; }
+int gw_patch_tile(int cin) { return cin > 32 ? 64 : 32; }
+int gw_patch_columns(int cin) { return (cin + gw_patch_tile(cin) - 1) / gw_patch_tile(cin); }
 
 // Weight and bias gradient over 4 x 16 patches (gw_patch(cin, cout)): dyb is dy as T.  About 1,024
 // blocks (four per compute unit), within the splits the partial buffer is sized for.
 template <typename T>
 hipError_t grad_weight_patch(const ConvIn<T> &in, const T *dyb, const float *dy, int n, int h, int w, int cin, int cout,
                              float *part, float *dw, float *db, hipStream_t st) {
-    const int ct = cin > 32 ? 64 : 32;
     const int tiles = n * ((h + GP_TH - 1) / GP_TH) * ((w + GP_TW - 1) / GP_TW);
-    const int gx = (cin + ct - 1) / ct, gy = (cout + 31) / 32;
+    const int gx = gw_patch_columns(cin), gy = (cout + 31) / 32;
     const int64_t most = std::min<int64_t>(gw_want_splits((int64_t)n * h * w, cin, cout), (1024 + gx * gy - 1) / (gx * gy));
     const int tps = (int)((tiles + most - 1) / most), splits = (tiles + tps - 1) / tps;
     const dim3 grid(gx, gy, splits);
-    if (ct == 64) k_conv3x3_gw_patch<T, 64><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
+    if (gw_patch_tile(cin) == 64) k_conv3x3_gw_patch<T, 64><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
     else k_conv3x3_gw_patch<T, 32><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
     sum_splits(part, splits, cin, cout, dw, db, st);
     return hipGetLastError();
@@ -1452,12 +1457,18 @@ hipError_t grad_weight_patch(const ConvIn<T> &in, const T *dyb, const float *dy,
 hipError_t conv3x3_grad_weight(const float *x, const float *dy, int n, int h, int w, int cin, int cout, float *part,
                                float *dw, float *db, hipStream_t st) {
     const int K = 9 * cin;
-    if (gw_patch(cin, cout) && (int64_t)n * h * w <= INT32_MAX && rows_fit(GP_TH + 2, w, std::max(cin, cout), sizeof(float)))
+    const int64_t pixels = (int64_t)n * h * w, padded = (int64_t)n * ((h + GP_TH - 1) / GP_TH * GP_TH) * ((w + GP_TW - 1) / GP_TW * GP_TW);
+    // Patches where images fill them at least by half and the launch has blocks enough for its longer per-patch work: the fewer
+    // the channel tiles and the emptier the patches, the more pixels.  Kernel times, tiled : patches, us: 512 -> 512 channels on
+    // 1 x 32^2 46 : 20, on 8 x 24^2 175 : 76, on 1 x 8^2 8.8 : 9.9, on 2048 x 4 278 : 343; 64 -> 64 on 1 x 32^2 11.3 : 13.5, on
+    // 64 x 8^2 12.8 : 22, on 2048 x 8 20 : 26; 16 -> 16 on 16 x 40 x 24 11.8 : 15.5.
+    const double ratio = (double)padded / pixels, blocks = (double)gw_patch_columns(cin) * ((cout + 31) / 32);
+    const bool fill = ratio <= 2.0 && pixels * blocks >= 16384.0 * ratio * ratio;
+    if (gw_patch(cin, cout) && fill && pixels <= INT32_MAX && rows_fit(GP_TH + 2, w, std::max(cin, cout), sizeof(float)))
         return grad_weight_patch<float>(ConvIn<float>{x, nullptr, cin, 0}, dy, dy, n, h, w, cin, cout, part, dw, db, st);
     if (gw_tiled(cin, cout)) {
-        const int64_t P = (int64_t)n * h * w;
-        const int64_t ps = gw_split_pixels(P, cin, cout);
-        const int64_t splits = (P + ps - 1) / ps;
+        const int64_t ps = gw_split_pixels(pixels, cin, cout);
+        const int64_t splits = (pixels + ps - 1) / ps;
         k_conv3x3_gw_tiled<<<dim3((K + 63) / 64, (cout + 63) / 64, (unsigned)splits), NT, 0, st>>>(
             x, dy, n, h, w, cin, cout, ps, part);
         sum_splits(part, splits, cin, cout, dw, db, st);

@@ -76,3 +76,18 @@ def test_network_of_narrow_layers(nn):
         k = int(np.prod(shp)) if shp else 1
         assert np.linalg.norm(g[o:o + k] - wg[o:o + k]) <= 2e-2 * np.linalg.norm(wg[o:o + k]), name
         o += k
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (1, 128, 128, 64, 32), (1, 127, 128, 32, 32), (1, 33, 31, 256, 248), (1, 16, 16, 136, 512),  # around the choice of kernel,
+    (512, 8, 8, 40, 64), (250, 8, 8, 72, 32), (700, 5, 4, 32, 64), (1, 2000, 3, 8, 24),  # half and quarter filled patches,
+    (1, 23, 24, 320, 320), (1, 70, 66, 8, 16)])  # few and many partial sums
+def test_grad_weight_variants(nn, n, h, w, cin, cout):
+    g = torch.Generator(device="cuda").manual_seed(cin + cout + h)
+    x, dy = (torch.randn(s, generator=g, device="cuda") for s in ((n, h, w, cin), (n, h, w, cout)))
+    dw, db = nn.conv3x3_grad_weight(x, dy)
+    qx, qy, f = U.bf16(x.cpu().numpy()), U.bf16(dy.cpu().numpy()), dy.cpu().numpy().astype(np.float64)
+    want, size = U.conv3x3_grad_weight(qx, qy)[0], U.conv3x3_grad_weight(np.abs(qx), np.abs(qy))[0]
+    P = n * h * w  # products of a weight's sum, and a few additions of partial sums
+    assert np.all(np.abs(dw.cpu().numpy() - want) <= (P + 8) * U24 * size + 1e-30)
+    assert np.all(np.abs(db.cpu().numpy() - f.sum(axis=(0, 1, 2))) <= (P + 8) * U24 * np.abs(f).sum(axis=(0, 1, 2)))
