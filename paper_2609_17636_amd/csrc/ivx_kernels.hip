@@ -1571,7 +1571,12 @@ __device__ __forceinline__ int ceildiv(int a, int b) { return -floordiv(-a, b); 
 // The beam sums split their taps over SD_ROW_P lanes (rows) and SD_COL_P (columns), SD_LOADS in flight
 // each: one thread per output was a chain of some 130 loads on 4 and 57 blocks, 28.6 and 16.5 us at 30^2
 // samples of a 480^2 sky and 35 and 19 at 64^2 of 1024^2, now 3.4, 3.7 and 5.2, 6.1.
+// Maps of every pixel that fill the chip with one lane an output (SD_FULL of them) keep that: neighbouring lanes read
+// neighbouring pixels then (512^2 of them 13 us, 15.2 split).  Launches are bounded and blocks run over the rest of
+// the outputs: the work items of a launch do not limit the size of a map.  (Columns on a sixteenth of these blocks took
+// 26.8 us at 512^2 instead of 22.)
 constexpr int SD_ROW_P = 8, SD_COL_P = 16, SD_LOADS = 8;
+constexpr int64_t SD_FULL = 1 << 18, SD_ROW_BLOCKS = 1 << 16, SD_COL_BLOCKS = 1 << 14;
 
 // sum over t = lo + part, lo + part + P, ... <= hi of gB[t + rb] v[t vs]
 template <int P> __device__ __forceinline__ real sd_taps(const real *__restrict__ gB, int rb, const real *__restrict__ v,
@@ -1592,21 +1597,22 @@ template <int P> __device__ __forceinline__ real sd_taps(const real *__restrict_
 }
 
 // U[c][i][q] = sum_j g(o + q S - j) x[c][i][j]   (beam along columns, sampled columns)
+template <int P>
 __global__ __launch_bounds__(NT) void k_sd_rows(Geom g, const real *__restrict__ sky,
                                                 const real *__restrict__ gB, int rb, int sd_n,
                                                 int stride, int offset, real *__restrict__ U) {
-    const int64_t idx = (int64_t)blockIdx.x * (NT / SD_ROW_P) + threadIdx.x / SD_ROW_P;
     const int64_t tot = (int64_t)g.C * g.N * sd_n;
-    if (idx >= tot) return;
-    const int q = (int)(idx % sd_n);
-    const int64_t ci = idx / sd_n; // c * N + i
-    const int cen = offset + q * stride;
-    const int lo = cen - rb < 0 ? -cen : -rb;
-    const int hi = cen + rb >= g.N ? g.N - 1 - cen : rb;
-    real s = sd_taps<SD_ROW_P>(gB, rb, sky + ci * g.N + cen, 1, lo, hi, threadIdx.x % SD_ROW_P);
+    for (int64_t idx = (int64_t)blockIdx.x * (NT / P) + threadIdx.x / P; idx < tot; idx += (int64_t)gridDim.x * (NT / P)) {
+        const int q = (int)(idx % sd_n);
+        const int64_t ci = idx / sd_n; // c * N + i
+        const int cen = offset + q * stride;
+        const int lo = cen - rb < 0 ? -cen : -rb;
+        const int hi = cen + rb >= g.N ? g.N - 1 - cen : rb;
+        real s = sd_taps<P>(gB, rb, sky + ci * g.N + cen, 1, lo, hi, threadIdx.x % P);
 #pragma unroll
-    for (int m = SD_ROW_P / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64); // (a group of lanes has one idx)
-    if (threadIdx.x % SD_ROW_P == 0) U[idx] = s;
+        for (int m = P / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64); // (a group of lanes has one idx)
+        if (threadIdx.x % P == 0) U[idx] = s;
+    }
 }
 
 // T~[c][p][q] = sum_i g(o + p S - i) U[c][i][q];  E = (T~ - T)/sigma^2;  K partials
@@ -1617,30 +1623,33 @@ __global__ __launch_bounds__(NT) void k_sd_cols(Geom g, const real *__restrict__
                                                 real inv_var, real *__restrict__ E, double *__restrict__ kpart) {
     constexpr int PER = NT / SD_COL_P;
     __shared__ real sums[NT];
-    const int64_t idx = (int64_t)blockIdx.x * PER + threadIdx.x % PER;
     const int64_t tot = (int64_t)g.C * sd_n * sd_n;
-    real s = real(0);
-    if (idx < tot) {
-        const int q = (int)(idx % sd_n);
-        const int p = (int)((idx / sd_n) % sd_n);
-        const int c = (int)(idx / ((int64_t)sd_n * sd_n));
-        const int cen = offset + p * stride;
-        const int lo = cen - rb < 0 ? -cen : -rb;
-        const int hi = cen + rb >= g.N ? g.N - 1 - cen : rb;
-        s = sd_taps<SD_COL_P>(gB, rb, U + ((int64_t)c * g.N + cen) * sd_n + q, sd_n, lo, hi, threadIdx.x / PER);
-    }
-    sums[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x >= 64) return;
     double kk = 0.0;
-    if (threadIdx.x < PER && idx < tot) {
-        real v = real(0);
+    for (int64_t first = (int64_t)blockIdx.x * PER; first < tot; first += (int64_t)gridDim.x * PER) { // (uniform)
+        const int64_t idx = first + threadIdx.x % PER;
+        real s = real(0);
+        if (idx < tot) {
+            const int q = (int)(idx % sd_n);
+            const int p = (int)((idx / sd_n) % sd_n);
+            const int c = (int)(idx / ((int64_t)sd_n * sd_n));
+            const int cen = offset + p * stride;
+            const int lo = cen - rb < 0 ? -cen : -rb;
+            const int hi = cen + rb >= g.N ? g.N - 1 - cen : rb;
+            s = sd_taps<SD_COL_P>(gB, rb, U + ((int64_t)c * g.N + cen) * sd_n + q, sd_n, lo, hi, threadIdx.x / PER);
+        }
+        sums[threadIdx.x] = s;
+        __syncthreads();
+        if (threadIdx.x < PER && idx < tot) {
+            real v = real(0);
 #pragma unroll
-        for (int part = 0; part < SD_COL_P; ++part) v += sums[part * PER + threadIdx.x];
-        const real res = v - sdmap[idx];
-        E[idx] = res * inv_var;
-        kk = 0.5 * (double)res * (double)res * (double)inv_var;
+            for (int part = 0; part < SD_COL_P; ++part) v += sums[part * PER + threadIdx.x];
+            const real res = v - sdmap[idx];
+            E[idx] = res * inv_var;
+            kk += 0.5 * (double)res * (double)res * (double)inv_var;
+        }
+        __syncthreads(); // (the sums are rewritten)
     }
+    if (threadIdx.x >= 64) return;
     for (int m = PER / 2; m >= 1; m >>= 1) kk += __shfl_xor(kk, m, 64);
     if (threadIdx.x == 0) kpart[blockIdx.x] = kk;
 }
@@ -2327,14 +2336,17 @@ hipError_t launch_grid(int mode, const Geom &g, const WorkItem *work, int n_work
 hipError_t launch_sd_rows(const Geom &g, const real *sky, const real *gB, int rb, int sd_n, int stride,
                           int offset, real *U, hipStream_t st) {
     const int64_t tot = (int64_t)g.C * g.N * sd_n;
-    constexpr int PER = NT / SD_ROW_P;
-    k_sd_rows<<<(unsigned)((tot + PER - 1) / PER), NT, 0, st>>>(g, sky, gB, rb, sd_n, stride, offset, U);
+    const bool one = stride == 1 && tot >= SD_FULL;
+    const int64_t per = one ? NT : NT / SD_ROW_P;
+    const unsigned blocks = (unsigned)std::min((tot + per - 1) / per, SD_ROW_BLOCKS);
+    if (one) k_sd_rows<1><<<blocks, NT, 0, st>>>(g, sky, gB, rb, sd_n, stride, offset, U);
+    else k_sd_rows<SD_ROW_P><<<blocks, NT, 0, st>>>(g, sky, gB, rb, sd_n, stride, offset, U);
     return hipGetLastError();
 }
 
 int sd_col_blocks(const Geom &g, int sd_n) {
     constexpr int PER = NT / SD_COL_P;
-    return (int)(((int64_t)g.C * sd_n * sd_n + PER - 1) / PER);
+    return (int)std::min(((int64_t)g.C * sd_n * sd_n + PER - 1) / PER, SD_COL_BLOCKS);
 }
 
 hipError_t launch_sd_cols(const Geom &g, const real *U, const real *gB, int rb, int sd_n, int stride,
