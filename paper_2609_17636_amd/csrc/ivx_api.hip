@@ -124,6 +124,7 @@ struct ivx_plan {
     uint64_t epoch = 0, fwd_epoch = ~0ull;
     const void *fwd_sky = nullptr;
     int tile_fixed = 0;
+    bool small_tiles = false; // the blocking is auto_blocking's faster choice, which takes more memory than roomy_blocking
     std::vector<real> dq_host;
     std::vector<cpx> tw_host;
     bool has_data = false;
@@ -436,33 +437,42 @@ ivx_status apply_geometry(ivx_plan *p, int W, int nf) {
 // other tile edges.  Where only one wave fits (double plans of 13-cell kernels and more) the smallest
 // tile: its blocks are the ones of which most fit a compute unit, and nothing is shared between waves
 // (nine 128^2 pointings of 200,000 visibilities 1088 us in 16-cell tiles, 817 in 13; 512^2 of 630,000 467 : 367;
-// 64^2 of 900 101 : 95).  ivx_autotune refines it by timing.
+// 64^2 of 900 101 : 95).  ivx_autotune refines it by timing.  Both take more memory than 16-cell tiles (double
+// plans 1.2 times the windows): a plan that they do not fit starts with those (roomy_blocking).
+bool roomy_blocking(ivx_plan *p) {
+    const int waves[] = {4, 2, 1};
+    const int cand[] = {16, 24, 12, 32, 8};
+    p->small_tiles = false;
+    for (int nw : waves)
+        for (int T : cand)
+            if (tile_fits(p, T, nw, 16)) {
+                p->nwave = nw;
+                p->lanes = 16;
+                p->vpi = 2;
+                set_tile(p, T);
+                return true;
+            }
+    return false;
+}
+
 bool auto_blocking(ivx_plan *p) {
     if (tile_fits(p, 17 - p->g.W, 1, GRID_MFMA_LANES)) {
         p->nwave = 1;
         p->lanes = GRID_MFMA_LANES;
         p->vpi = 1;
         set_tile(p, 17 - p->g.W);
+        p->small_tiles = true;
         return true;
     }
-    const int waves[] = {4, 2};
-    const int cand[] = {16, 24, 12, 32, 8};
-    for (int nw : waves)
-        for (int T : cand)
-            if (tile_fits(p, T, nw, 16)) {
-                p->nwave = nw;
-                p->lanes = 16;
-                set_tile(p, T);
-                return true;
-            }
-    for (int T = p->g.W; T <= 32; ++T)
+    if (!roomy_blocking(p)) return false;
+    if (p->nwave > 1) return true;
+    for (int T = p->g.W; T < p->g.T; ++T)
         if (tile_fits(p, T, 1, 16)) {
-            p->nwave = 1;
-            p->lanes = 16;
             set_tile(p, T);
-            return true;
+            p->small_tiles = true;
+            break;
         }
-    return false;
+    return true;
 }
 
 // Plan-time temporary device buffer (not counted in the plan's memory).
@@ -1378,6 +1388,7 @@ ivx_status ivx_set_blocking(ivx_plan *p, int32_t tile, int32_t waves, int32_t ch
         return fail(IVX_EINVAL, "blocking out of range");
     if (!tile_fits(p, tile, waves, lanes)) return fail(IVX_EINVAL, "blocking does not fit the LDS");
     ++p->epoch;
+    p->small_tiles = false;
     p->nwave = waves;
     p->chunk_max = chunk;
     p->lanes = lanes;
@@ -1521,19 +1532,27 @@ ivx_status ivx_plan_set_w(ivx_plan *p, const ivx_real *w, int32_t w_width, doubl
     if (!std::isfinite(sigma) || sigma < 1.25 || sigma > 8.0) return fail(IVX_EINVAL, "w_sigma must be 0 or in [1.25, 8]");
     hipStream_t st = (hipStream_t)stream;
     IVX_HIP(hipStreamSynchronize(st));
-    p->w_on = false;
-    ivx_status s = w_tables(p, Ww, sigma);
-    if (s != IVX_OK) return s;
-    const int64_t n = p->shared_uv ? p->pt_off.back() : p->m_total;
-    if (!p->d_wsrc && (s = dalloc(p, &p->d_wsrc, (size_t)std::max<int64_t>(n, 1))) != IVX_OK) return s;
-    if (n > 0) IVX_HIP(hipMemcpy(p->d_wsrc, w, n * sizeof(real), hipMemcpyDefault));
-    p->w_on = true;
-    p->w_version = ~0ull;
-    if ((s = w_prepare(p, st)) != IVX_OK) {
+    auto set = [&]() {
         p->w_on = false;
+        ivx_status s = w_tables(p, Ww, sigma);
+        if (s != IVX_OK) return s;
+        const int64_t n = p->shared_uv ? p->pt_off.back() : p->m_total;
+        if (!p->d_wsrc && (s = dalloc(p, &p->d_wsrc, (size_t)std::max<int64_t>(n, 1))) != IVX_OK) return s;
+        if (n > 0) IVX_HIP(hipMemcpy(p->d_wsrc, w, n * sizeof(real), hipMemcpyDefault));
+        p->w_on = true;
+        p->w_version = ~0ull;
+        if ((s = w_prepare(p, st)) != IVX_OK) p->w_on = false;
         return s;
+    };
+    ivx_status s = set();
+    if (s == IVX_ENOMEM && p->small_tiles && roomy_blocking(p)) {
+        g_last_error.clear();
+        drop_graph(p);
+        free_one(p, p->d_slots); // (the records are sorted in its place)
+        p->d_slots = nullptr;
+        if ((s = build_bins(p, st)) == IVX_OK) s = set();
     }
-    return IVX_OK;
+    return s;
 }
 
 ivx_status ivx_plan_w_info(const ivx_plan *p, double *info) {
@@ -1547,8 +1566,8 @@ ivx_status ivx_plan_w_info(const ivx_plan *p, double *info) {
 
 namespace {
 
-ivx_status set_data_impl(ivx_plan *p, const VisSource &src, bool shared, const ivx_real *beams,
-                         const ivx_real *interp, const ivx_real *sd_map, void *stream) {
+ivx_status set_data_blocked(ivx_plan *p, const VisSource &src, bool shared, const ivx_real *beams,
+                            const ivx_real *interp, const ivx_real *sd_map, void *stream) {
     const int64_t M = p->m_total;
     if (M > 0 && (!src.uv || !src.vis || !src.w)) return fail(IVX_EINVAL, "uv, vis and weight are required");
     if (!beams || !interp) return fail(IVX_EINVAL, "beams and interp are required");
@@ -1719,6 +1738,16 @@ fail_free:
         const std::string msg = g_last_error;
         free_all(p);
         g_last_error = msg;
+    }
+    return s;
+}
+
+ivx_status set_data_impl(ivx_plan *p, const VisSource &src, bool shared, const ivx_real *beams,
+                         const ivx_real *interp, const ivx_real *sd_map, void *stream) {
+    ivx_status s = set_data_blocked(p, src, shared, beams, interp, sd_map, stream);
+    if (s == IVX_ENOMEM && p->small_tiles && roomy_blocking(p)) {
+        g_last_error.clear();
+        s = set_data_blocked(p, src, shared, beams, interp, sd_map, stream);
     }
     return s;
 }
@@ -1958,6 +1987,7 @@ ivx_status ivx_autotune(ivx_plan *p, double budget_ms, int32_t *chosen_tile, voi
                             for (int ch : chunks) c.push_back(Cand{W, nf, T, nw, ch, lanes, vpi});
         return c;
     };
+    p->small_tiles = false; // (the blocking becomes the search's choice)
     // whole evaluations at a zero sky on the plan's own data (the geometry changes the FFT
     // passes too); the fastest candidate is kept
     real *sky = nullptr, *grad = nullptr;

@@ -48,3 +48,48 @@ def test_default_blocking_agrees_with_the_vector_gridder(mini, width):
 
 def test_double_plans_start_with_the_vector_gridder(mini):
     assert Plan.from_problem(mini, precision="f64").info()["lanes"] == 16
+
+
+@pytest.mark.parametrize("w", [False, True])
+def test_a_plan_that_small_tiles_do_not_fit_starts_with_larger_ones(w):
+    """The card is filled, in pieces smaller than what the default takes beyond 16-cell tiles, until the default
+    does not fit any more."""
+    n_sub, points, per = 64, 24, 200000
+    rng = np.random.default_rng(1)
+    grid = np.stack(np.meshgrid(np.arange(n_sub), np.arange(n_sub), indexing="ij"), axis=-1)
+    arr = dict(uv=rng.uniform(-1e4, 1e4, (points * per, 2)), vis=rng.standard_normal((points * per, 2)),
+               weight=np.ones(points * per), beams=np.ones((points, n_sub, n_sub)),
+               interp=np.broadcast_to(grid, (points, n_sub, n_sub, 2)))
+    arr = {k: torch.tensor(np.ascontiguousarray(v, dtype=np.float32), device="cuda") for k, v in arr.items()}
+    uvw = torch.tensor(rng.uniform(0, 10, points * per), dtype=torch.float32, device="cuda") if w else None
+    x = torch.tensor(rng.uniform(0, 1, (1, n_sub, n_sub)), dtype=torch.float32, device="cuda")
+
+    def plan(blocking=None):
+        p = Plan(1, n_sub, 5e-5, points, n_sub, per * np.arange(points + 1), [1.0], kernel_width=8, fine_size=2048)
+        if blocking:
+            p.set_blocking(*blocking)
+        p.set_data(**arr)
+        if w:
+            p.set_w(uvw)
+        return p
+
+    p = plan((16, 4, 256, 16, 2))
+    need, want = p.info()["device_bytes"], p.objective_grad(x)
+    p.close()
+    p = plan()
+    more = p.info()["device_bytes"] - need
+    assert p.info()["lanes"] == 64 and more > 2 ** 28
+    p.close()
+    torch.cuda.empty_cache()
+    fill = [torch.empty(torch.cuda.mem_get_info()[0] - need - more, dtype=torch.uint8, device="cuda")]
+    for _ in range(64):  # (some more than is reported as free can be allocated)
+        p = plan()
+        if p.info()["lanes"] != 64:
+            break
+        p.close()
+        fill.append(torch.empty(more // 3, dtype=torch.uint8, device="cuda"))
+    assert p.info()["lanes"] == 16 and p.info()["device_bytes"] == need
+    terms, grad = p.objective_grad(x)
+    del fill
+    torch.cuda.empty_cache()
+    assert np.array_equal(terms, want[0]) and torch.equal(grad, want[1])
