@@ -720,7 +720,8 @@ ivx_status build_work(ivx_plan *p, hipStream_t st) {
     Geom &g = p->g;
     const int n_items = g.C * g.P;
     const int ntiles = p->bin_ntiles;
-    const int chunk_max = p->chunk_max;
+    // (the matrix-core gridder takes 32-bit byte offsets from a work item's first record, 8 bytes each)
+    const int chunk_max = p->lanes == GRID_MFMA_LANES ? std::min(p->chunk_max, 1 << 28) : p->chunk_max;
     std::vector<int32_t> tslot((size_t)n_items * (ntiles + 1), 0);
     std::vector<WorkItem> work;
     int64_t slot = 0;

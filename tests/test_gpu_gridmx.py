@@ -78,3 +78,26 @@ def test_zero_residual_and_zero_sky():
     plan.set_problem_data(p)
     terms, grad = plan.objective_grad(torch.zeros((1, 32, 32), dtype=torch.float32, device="cuda"))
     assert terms[0] == 0.0 and float(grad.abs().max()) == 0.0
+
+
+def test_more_records_in_a_tile_than_32_bit_offsets_reach():
+    """2^29 + 100,000 visibilities of one tile under a chunk that would take them all: the last ones are their own."""
+    n, count, pix = 16, (1 << 29) + 100000, 1e-4
+    g = torch.Generator(device="cuda").manual_seed(1)
+    uv = torch.rand((count, 2), generator=g, device="cuda").mul_(2.0).add_(1000.0)
+    plan = Plan(1, n, pix, 1, n, [0, count], [1.0], kernel_width=8, fine_size=64)
+    plan.set_blocking(9, 1, 1 << 30, 64, 1)
+    i = torch.arange(n, device="cuda", dtype=torch.float32)
+    grid = torch.stack(torch.meshgrid(i, i, indexing="ij"), dim=-1)[None]
+    vis, weight = torch.zeros((count, 2), device="cuda"), torch.ones(count, device="cuda")
+    plan.set_data(uv, vis, weight, torch.ones((1, n, n), device="cuda"), grid)
+    del vis, weight
+    torch.cuda.empty_cache()
+    assert plan.info()["n_work_items"] == 3
+    x = torch.zeros((1, n, n), device="cuda")
+    x[0, 2, 3] = 1.0  # direction cosines (3 - 8, 2 - 8) pix
+    v = plan.forward(x)
+    for s in (slice(0, 100000), slice(count - 100000, count)):
+        ph = -2.0 * np.pi * pix * (uv[s].double() @ torch.tensor([-5.0, -6.0], dtype=torch.float64, device="cuda"))
+        want = torch.stack([torch.cos(ph), torch.sin(ph)], dim=1)
+        assert float((v[s].double() - want).abs().max()) <= TOL * 10  # (of single values, not of a norm)
