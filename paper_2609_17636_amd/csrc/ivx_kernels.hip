@@ -683,12 +683,19 @@ int grid_groups_per_wave(int W, int lanes) { return (lanes == 8 && W <= 8) ? 8 :
 // Arithmetic.  Every factor is split into two half-precision parts, x = h + l with h the
 // nearest half and l the nearest half to x - h, and a product is the three matrix products
 // h h' + h l' + l h' accumulated in FP32 (v_mfma_f32_32x32x16_f16, v_mfma_f32_16x16x32_f16).
-// The parts together hold 22 bits and a sign, and the dropped l l' is below 2^-24 of h h', so a
-// product carries the rounding of an FP32 one: against FP64, dot products of 32 and of 256
-// normal deviates are 8.2e-8 and 2.0e-7 off, 1.1e-7 and 2.8e-7 on v_mfma_f32_16x16x4_f32.  Halves
-// reach down to 2^-24, so the window and w r are scaled by powers of two (exactly): the window by
+// A half has 11 bits, so |l| is at most 2^-11 |x|, the pair is x to 2^-24 of the power of two above |x| (one FP32
+// unit, for a quarter of the values), and the dropped l l' reaches 2^-22 of h h': at worst a product is 2^-21
+// off, eight times an FP32 one.  On average the matrix instructions' fewer roundings of the sum make up for it: dot
+// products of 32 and of 256 normal deviates are 8.2e-8 and 2.0e-7 off, 1.1e-7 and 2.8e-7 on v_mfma_f32_16x16x4_f32.
+// Whole calls (L2 error against 64 bits, geometric mean of 21 problems; in brackets this kernel on FP32 products with the
+// same weights): gradient 2.52e-7 (2.48), model 3.31e-7 (3.18), adjoint 2.28e-7 (2.24); the kernel on FP32 products
+// that it replaced, whose weights carried the rounding of the square root and of the exponent's constant, 6.2, 5.0
+// and 4.6e-7.  With l l' they are 2.49, 3.28 and 2.26e-7, for 5% of the time.
+// Halves reach down to 2^-24, so the window and w r are scaled by powers of two (exactly): the window by
 // its largest value, w r by a scale of the work item that is lowered, with H, when a batch
-// exceeds it; weights are at most 1 and keep 2^-25 of the peak.
+// exceeds it; weights are at most 1 and keep 2^-24 of the peak.  A record 2^17 and more below its item's largest has
+// fewer bits; what it loses is 2^-39 of the largest, whose own FP32 rounding is 2^-24 of it.  (Adjoints of data that spread
+// over 2^20 and 2^40, or with one or 1% of the samples 10^6 and 10^7 times the rest, are off as they are on FP32 products.)
 //
 // What bounds it: instruction issue.  A wave64 vector instruction takes 4 cycles of its SIMD, an
 // exponential or square root 8, and a matrix instruction holds the SIMD's issue for 16 whatever
@@ -697,10 +704,11 @@ int grid_groups_per_wave(int W, int lanes) { return (lanes == 8 && W <= 8) ? 8 :
 // (m = l % 32, axis l / 32), stored to a row of LDS between zeros that are never overwritten, and
 // read back at the window's fixed positions as a row shifted by the footprint's start: no
 // per-batch clearing and no test of the footprint's bounds.  The K = m operands of the spread are
-// rows [m][position] read through the transposing LDS load.  About 165 vector instructions and 9 matrix
-// instructions a batch at W = 7, 883 cycles of a SIMD with a work item's share.  Measured against FP32 matrix products in batches
-// of 16 (950 cycles each): 790 -> 450 us on 34 M visibilities of 36 pointings, 7.8 -> 5.2 ms on
-// eight channels of them, 28 -> 19 us on one 512^2 pointing of 630,000.
+// rows [m][position] read through the transposing LDS load.  157 vector instructions (14 of them exponentials and
+// roots) and 9 matrix instructions a batch at W = 7, and some 290 an item: 883 cycles of a SIMD a batch with its share
+// of the item's (seven batches an item on the 128-channel cube).  Measured against FP32 matrix products in batches
+// of 16 (gridding alone): 845 -> 481 us on the 31.7 M visibilities of 36 pointings in 192,831 items, 122.0 -> 81.7 ms on
+// 128 channels of them (5.1e9 in 24.7 M), 29 -> 19.7 us on one 512^2 pointing of 630,000.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -710,8 +718,8 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int MX_B = 32;             // visibilities per batch
 constexpr int MX_FBITS = 14;         // the window's largest value lies in [2^14, 2^15)
-constexpr int MX_RBITS = 10;         // a new scale puts the largest |w r| in [2^10, 2^11) ...
-constexpr float MX_RMAX = 32768.f;   // ... and is kept while they stay below this (weights are <= 1)
+constexpr int MX_RBITS = 14;         // a new scale puts the largest |w r| in [2^14, 2^15) ...
+constexpr float MX_RMAX = 65000.f;   // ... and is kept while they stay below this (weights are <= 1)
 
 // LDS hand-off between the lanes of the (single-wave) block: a wave's LDS operations are
 // performed in order, so only the compiler has to be kept from moving accesses across;
@@ -760,7 +768,7 @@ __device__ __forceinline__ int scale_bits(float x, int bits) {
 
 __device__ __forceinline__ float exp2_int(int e) { return __uint_as_float((unsigned)(e + 127) << 23); } // |e| <= 126
 
-// Eight values as halves hi + lo: x = hi + lo to 2^-25 of the power of two above |x| (and to
+// Eight values as halves hi + lo: x = hi + lo to 2^-24 of the power of two above |x| (and to
 // 2^-25 absolutely).  m1 is -1 in a register the compiler cannot see through: x - hi is then one
 // mixed-precision multiply-add on the half instead of a conversion back and a subtraction.
 __device__ __forceinline__ void split_halves(const float (&x)[8], float m1, f16x8 &hi, f16x8 &lo) {
@@ -794,13 +802,8 @@ __device__ __forceinline__ f16x8 column_operand(const _Float16 *at) {
 }
 
 // KW > 0 fixes the kernel width at compile time; KW = 0 reads it from the geometry.
-// Measured (gridding of the 36-pointing mosaic, 31.7 M visibilities in 192,831 items / of eight cube
-// channels, 318 M in 1.54 M items / of the 512^2 single pointing): 438 us / 5.01 ms / 19.5 us;
-// the 16-visibility batches of v_mfma_f32_16x16x4_f32 before took 790 us / 7.75 ms / 28.5 us.  A
-// batch takes 155 vector instructions and an item 190: 92% of the issue time on the mosaic.  The LDS
-// (7.7 KB, one table at a time) admits five waves per SIMD; all three tables at once left four
-// (457 us / 5.18 ms), and weight rows by visibility instead of by position cost 512 -> 605 us in
-// bank conflicts.
+// The LDS (7.7 KB, one table of the spread at a time) admits five waves per SIMD; all three tables at once left four
+// (4% slower), and weight rows by visibility instead of by position cost 18% in bank conflicts.
 template <int MODE, int KW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_gridmx(GridArgs a) {
     constexpr bool WPL = MODE == MODE_WFWD || MODE == MODE_WADJ; // one w plane of the full model
