@@ -296,7 +296,7 @@ ivx_status ivx_set_blocking(ivx_plan *plan, int32_t tile, int32_t waves, int32_t
                             int32_t lanes, int32_t vpi, void *stream);
 
 /* Register budget of the matrix-core gridder (blockings with 64 lanes per visibility): 6 or 7
- * resident waves per SIMD, or 0 (the default).  The gridder's LDS now admits four, so one build
+ * resident waves per SIMD, or 0 (the default).  The gridder's LDS admits five, so one build
  * serves every setting and the call only checks its argument.  IVX_EINVAL otherwise. */
 ivx_status ivx_set_gridder_occupancy(ivx_plan *plan, int32_t waves_per_simd);
 

@@ -1406,9 +1406,7 @@ ivx_status ivx_set_gridder_occupancy(ivx_plan *p, int32_t waves_per_simd) {
     if (!p) return fail(IVX_EINVAL, "plan is NULL");
     if (!(waves_per_simd == 0 || waves_per_simd == 6 || waves_per_simd == 7))
         return fail(IVX_EINVAL, "waves_per_simd must be 0 (automatic), 6 or 7");
-    // one build serves every setting (include/ivx.h)
-    drop_graph(p); // the captured launches name the build
-    return IVX_OK;
+    return IVX_OK; // one build serves every setting
 }
 
 ivx_status ivx_set_fused_fold(ivx_plan *p, int enable) {

@@ -101,3 +101,19 @@ def test_more_records_in_a_tile_than_32_bit_offsets_reach():
         ph = -2.0 * np.pi * pix * (uv[s].double() @ torch.tensor([-5.0, -6.0], dtype=torch.float64, device="cuda"))
         want = torch.stack([torch.cos(ph), torch.sin(ph)], dim=1)
         assert float((v[s].double() - want).abs().max()) <= TOL * 10  # (of single values, not of a norm)
+
+
+def test_occupancy_setting_keeps_the_captured_evaluation():
+    """One build serves every setting: nothing of the plan changes with it."""
+    p = _problem(500)
+    plan = Plan.from_problem(p, precision="f32")
+    plan.set_problem_data(p)
+    x = torch.rand((1, 32, 32), device="cuda")
+    grad = torch.empty_like(x)
+    terms, _ = plan.objective_grad(x, grad=grad)
+    want, nodes = grad.clone(), plan.info()["graph_nodes"]
+    assert nodes > 0
+    for waves in (6, 7, 0):
+        plan.set_gridder_occupancy(waves)
+        assert plan.info()["graph_nodes"] == nodes
+        assert np.array_equal(plan.objective_grad(x, grad=grad)[0], terms) and torch.equal(grad, want)
