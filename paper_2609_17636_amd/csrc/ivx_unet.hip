@@ -485,6 +485,33 @@ k_conv3x3_wave(ConvIn<T> in, int n, int h, int w, int cin, const uint16_t *__res
     }
 }
 
+// Network layers on images whose rows are too long for 32-bit offsets into the three rows of a pixel (2^28 and more channels a row):
+// 16 pixels x 16 channels a wave at 64-bit addresses.
+__global__ __launch_bounds__(NT) void k_conv3x3_far(ConvIn<uint16_t> in, int n, int h, int w, int cin,
+                                                    const uint16_t *__restrict__ wt, int packed, int cout, ConvOut out) {
+    const int lane = threadIdx.x & 63, row = lane & 15, kq = lane >> 4;
+    const int64_t P = (int64_t)n * h * w, p = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 + row, q = p < P ? p : P - 1;
+    const int64_t img = q / ((int64_t)h * w);
+    const int py = (int)((q - img * h * w) / w), px = (int)(q - (img * h + py) * w);
+    const int n0 = blockIdx.y * 16, K = 9 * cin, ca = in.ca, cb = cin - in.ca;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        const int k = k0 + 8 * kq, t = k / cin, c = k - t * cin, yy = py + t / 3 - 1, xx = px + t % 3 - 1;
+        uint4 a = {0u, 0u, 0u, 0u}, b = {0u, 0u, 0u, 0u};
+        if (k < K) {
+            b = *reinterpret_cast<const uint4 *>(
+                wt + (packed ? ((int64_t)(n0 >> 4) * (K >> 5) + (k >> 5)) * 512 + 8 * lane : (int64_t)(n0 + row) * K + k));
+            if (p < P && yy >= 0 && yy < h && xx >= 0 && xx < w) {
+                const int sh = c < ca ? in.half0 : 0;
+                const int64_t pix = (img * (h >> sh) + (yy >> sh)) * (w >> sh) + (xx >> sh);
+                a = *reinterpret_cast<const uint4 *>(c < ca ? in.x0 + pix * ca + c : in.x1 + pix * cb + (c - ca));
+            }
+        }
+        acc = mma(as_bf16x8(b), as_bf16x8(a), acc);
+    }
+    if (p < P) store_out(out, acc, p, img, py, px, h, w, cout, n0 + 4 * kq);
+}
+
 // A block of WM x WN waves owns 2 WM rows x 32 columns of one image and 16 NJ WN output channels.  The
 // patch with its one-pixel halo is staged in LDS once, all input channels of it (the order of the steps
 // runs over channels inside the taps) or, where these do not fit, cp at a time, and serves the nine taps; the weights stay in the vector cache,
@@ -808,7 +835,8 @@ __device__ __forceinline__ s16x4 read_columns(const uint16_t *at) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
 }
 
-template <typename T, int CT>
+// FAR: images whose rows are too long for 32-bit offsets into a patch's rows (plain loads at 64-bit addresses).
+template <typename T, int CT, bool FAR = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_conv3x3_gw_patch(ConvIn<T> in, const T *__restrict__ dyb,
                                                          const float *__restrict__ dy, int n, int h, int w, int cin,
                                                          int cout, int tiles, int tps, float *__restrict__ part) {
@@ -833,6 +861,26 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 8))) void
         const int img = t / (tx * ty), r = t - img * tx * ty, y0 = (r / tx) * GP_TH, x0 = (r % tx) * GP_TW;
         // views of this image: offsets stay small whatever the batch
         const int64_t base = (int64_t)img * h * w, base0 = in.half0 ? (int64_t)img * (h >> 1) * (w >> 1) : base;
+        if constexpr (FAR) {
+            const int yy = y0 + (dp >> 4), xx = x0 + (dp & 15);
+            const bool okp = yy < h && xx < w && dc < cout;
+            const int64_t at = (base + (int64_t)yy * w + xx) * cout + dc;
+            rd = uint4{0u, 0u, 0u, 0u};
+            if (okp) rd = *reinterpret_cast<const uint4 *>(dyb + at);
+            if (do_bias && okp)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) bs[e] += dy[at + e];
+#pragma unroll
+            for (int u = 0; u < XPER; ++u) {
+                const int e = tid + u * NT, pos = e / (CT / 8), c = c0 + 8 * (e % (CT / 8));
+                const int yx = y0 - 1 + pos / GP_PW, xp = x0 - 1 + pos % GP_PW, sh = c < ca ? in.half0 : 0;
+                const int64_t pix = (c < ca ? base0 : base) + (int64_t)(yx >> sh) * (w >> sh) + (xp >> sh);
+                rx[u] = uint4{0u, 0u, 0u, 0u};
+                if (e < XPIECES && c < cin && yx >= 0 && yx < h && xp >= 0 && xp < w)
+                    rx[u] = *reinterpret_cast<const uint4 *>(c < ca ? in.x0 + pix * ca + c : in.x1 + pix * cb + (c - ca));
+            }
+            return;
+        }
         {
             const int yy = y0 + (dp >> 4), xx = x0 + (dp & 15);
             const bool okp = yy < h && xx < w && dc < cout;
@@ -1354,6 +1402,11 @@ hipError_t conv3x3(const ConvIn<T> &in, int n, int h, int w, int cin, const uint
         IVX_PATCH(1, 2, 1, 9);
 #undef IVX_PATCH
     }
+    if constexpr (sizeof(T) == 2)
+        if (!rows_fit(4, w, cin, sizeof(T))) {
+            k_conv3x3_far<<<dim3((unsigned)((P + 63) / 64), cout / 16), NT, 0, st>>>(in, n, h, w, cin, wt, packed, cout, out);
+            return hipGetLastError();
+        }
     constexpr int64_t FULL = 2048;
     if (cout % 64 == 0 && waves(4, 4) >= FULL) conv3x3_wave<T, 4, 4, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
     else if (cout % 32 == 0 && waves(4, 2) >= FULL) conv3x3_wave<T, 4, 2, 2>(in, n, h, w, cin, wt, packed, cout, chunks, out, st);
@@ -1448,8 +1501,11 @@ hipError_t grad_weight_patch(const ConvIn<T> &in, const T *dyb, const float *dy,
     const int64_t most = std::min<int64_t>(gw_want_splits((int64_t)n * h * w, cin, cout), (1024 + gx * gy - 1) / (gx * gy));
     const int tps = (int)((tiles + most - 1) / most), splits = (tiles + tps - 1) / tps;
     const dim3 grid(gx, gy, splits);
-    if (gw_patch_tile(cin) == 64) k_conv3x3_gw_patch<T, 64><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
-    else k_conv3x3_gw_patch<T, 32><<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
+    const bool far = sizeof(T) == 2 && !rows_fit(GP_TH + 2, w, std::max(cin, cout), sizeof(float)); // (FP32 layers: the tiled kernel)
+    auto kernel = gw_patch_tile(cin) == 64 ? k_conv3x3_gw_patch<T, 64> : k_conv3x3_gw_patch<T, 32>;
+    if constexpr (sizeof(T) == 2)
+        if (far) kernel = gw_patch_tile(cin) == 64 ? k_conv3x3_gw_patch<T, 64, true> : k_conv3x3_gw_patch<T, 32, true>;
+    kernel<<<grid, NT, 0, st>>>(in, dyb, dy, n, h, w, cin, cout, tiles, tps, part);
     sum_splits(part, splits, cin, cout, dw, db, st);
     return hipGetLastError();
 }

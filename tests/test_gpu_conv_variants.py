@@ -91,3 +91,48 @@ def test_grad_weight_variants(nn, n, h, w, cin, cout):
     P = n * h * w  # products of a weight's sum, and a few additions of partial sums
     assert np.all(np.abs(dw.cpu().numpy() - want) <= (P + 8) * U24 * size + 1e-30)
     assert np.all(np.abs(db.cpu().numpy() - f.sum(axis=(0, 1, 2))) <= (P + 8) * U24 * np.abs(f).sum(axis=(0, 1, 2)))
+
+
+def test_network_on_very_long_rows(nn):
+    """Rows of 12,000,000 pixels, of which four are beyond 32-bit offsets: the same as eight images of an eighth of the
+    row whose pixels within reach of a seam are zero.  Activations may round the other way where sums differ in their
+    order (2^-9 of a few): 1e-3 of the norm."""
+    pieces, w, h = 8, 1500000, 4
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x, t = (torch.rand((pieces, h, w), generator=g, device="cuda") for _ in range(2))
+    for a in (x, t):
+        a[:, :, :64] = 0.0
+        a[:, :, -64:] = 0.0
+    out = []
+    for batch in (pieces, 1):
+        net = nn.UNet(levels=2, base=16, max_batch=batch, height=h, width=pieces * w // batch, seed=3)
+        if batch == 1:
+            x, t = (a.transpose(0, 1).reshape(1, h, pieces * w).contiguous() for a in (x, t))
+        y = net.forward(x)
+        if batch > 1:
+            y = y.transpose(0, 1).reshape(1, h, pieces * w)
+        loss, grads = net.loss_grad(x, t)
+        out.append((y.clone(), loss, torch.as_tensor(grads).double().cpu().numpy()))
+        net.close()
+    (y0, l0, g0), (y1, l1, g1) = out
+    assert float((y1 - y0).norm()) <= 1e-3 * float(y0.norm())
+    assert abs(l1 - l0) <= 1e-3 * abs(l0)
+    assert np.linalg.norm(g1 - g0) <= 1e-3 * np.linalg.norm(g0)
+
+
+@pytest.mark.parametrize("cin,cout", [(256, 128), (640, 96), (40, 64), (24, 32)])
+def test_layers_in_a_captured_graph(nn, cin, cout):
+    """Layers whose blocks ask for more than the default LDS among them: every replay gives the eager bits."""
+    g = torch.Generator(device="cuda").manual_seed(cin)
+    x, wt = torch.randn((2, 40, 36, cin), generator=g, device="cuda"), torch.randn((cout, 3, 3, cin), generator=g, device="cuda")
+    wb, y = nn.to_bf16(wt), torch.zeros((2, 40, 36, cout), device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        nn.conv3x3(x, wb, out=y)
+    for seed in range(3):
+        x.copy_(torch.randn(x.shape, generator=g, device="cuda"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, nn.conv3x3(x, wb))
