@@ -429,14 +429,14 @@ ivx_status apply_geometry(ivx_plan *p, int W, int nf) {
 }
 
 // Default blocking.  Float plans of kernels up to 8 cells: the matrix-core gridder at its largest tile
-// (window 16), which is the faster one over the whole range: against the vector gridder's default 86 : 162 us
+// (window 16), which is the faster one over the whole range: against the vector gridder's default 79 : 153 us
 // (six pointings of 150^2 and 157,000 visibilities, forward and adjoint), 341 : 1194 (15 x 112^2 x
 // 1,067,000), 116 : 229 (one 64^2 field of 1,000,000), 72 : 77 (256^2 of 3,000) and within the runs'
 // spread at the smallest (64^2 of 20,000: 71 : 71).  Its windows take up to 1.5 times the memory.  Otherwise the vector
 // gridder: the widest block (4 waves) and a 16-cell tile when they fit the LDS budget, else 2 waves, else
 // other tile edges.  Where only one wave fits (double plans of 13-cell kernels and more) the smallest
 // tile: its blocks are the ones of which most fit a compute unit, and nothing is shared between waves
-// (nine 128^2 pointings of 200,000 visibilities 1088 us in 16-cell tiles, 817 in 13; 512^2 of 630,000 467 : 367;
+// (nine 128^2 pointings of 200,000 visibilities 1,135 us in 16-cell tiles, 840 in 13; 512^2 of 630,000 467 : 367;
 // 64^2 of 900 101 : 95).  ivx_autotune refines it by timing.  Both take more memory than 16-cell tiles (double
 // plans 1.2 times the windows): a plan that they do not fit starts with those (roomy_blocking).
 bool roomy_blocking(ivx_plan *p) {

@@ -707,7 +707,7 @@ int grid_groups_per_wave(int W, int lanes) { return (lanes == 8 && W <= 8) ? 8 :
 // rows [m][position] read through the transposing LDS load.  157 vector instructions (14 of them exponentials and
 // roots) and 9 matrix instructions a batch at W = 7, and some 290 an item: 883 cycles of a SIMD a batch with its share
 // of the item's (seven batches an item on the 128-channel cube).  Measured against FP32 matrix products in batches
-// of 16 (gridding alone): 845 -> 481 us on the 31.7 M visibilities of 36 pointings in 192,831 items, 122.0 -> 81.7 ms on
+// of 16 (gridding alone): 845 -> 481 us on 34.4 M visibilities of 36 pointings in 192,839 items, 122.0 -> 81.7 ms on
 // 128 channels of them (5.1e9 in 24.7 M), 29 -> 19.7 us on one 512^2 pointing of 630,000.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
