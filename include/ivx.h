@@ -106,7 +106,8 @@ typedef struct {
     double nufft_eps;           /* requested NUFFT accuracy (0 = 1e-7 float, 1e-12 double) */
     int32_t kernel_width;       /* spreading kernel width in fine cells (0 = from eps) */
     int32_t fine_size;          /* fine grid n_f, power of two >= 2 n_sub (0 = auto) */
-    int32_t tile;               /* gridding tile edge in fine cells (0 = auto) */
+    int32_t tile;               /* gridding tile edge in fine cells (0 = auto: the faster of two, the one that takes
+                                   less memory when the faster one's windows do not fit) */
     int32_t reserved;           /* must be 0 */
     double lambda_nu;           /* spectral smoothness weight, >= 0 (0 = channels independent) */
 } ivx_problem;
